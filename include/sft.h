@@ -351,8 +351,8 @@ enum { SFT_ORDER_GIVEN = 0, SFT_ORDER_TRACK = 1 };
  * Launch shape of the bank scan, kept per data handle (fields equal to 0 select the
  * automatic choice).  block: templates per workgroup, 64, 128 or 256 (default 256).
  * chunk_groups: timestamp groups (SFT rows sharing a start time, one per detector) per
- * work item; a work item is (template tile, chunk), and partial sums are combined in
- * chunk order (default: chunks of about 1 MiB of bins and at least four work items per
+ * work item; a work item is (template tile, chunk), and partial sums are combined in a
+ * fixed order (default: chunks of about 1 MiB of bins and at least four work items per
  * resident workgroup).  persistent: 1 launches one workgroup per resident slot, each
  * pulling work items from a device counter until the queue is empty; 0 launches one
  * workgroup per item.  An all-zero tuning selects the automatic chunks with the
