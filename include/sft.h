@@ -123,8 +123,8 @@ void sft_free_data(sft_data* data);
  * Each detector's series is cut into consecutive segments of n samples, segment a covering
  * samples [a n, (a+1) n) and starting at t0 + a n dt; a segment holding a non-finite sample is
  * a data gap (missing SFT).  n a power of two: an FFT per segment; other even n (the SFT
- * lengths of Sec. IV, e.g. 106 s at 40 Hz) with a known white PSD: the band bins by their
- * defining sum.
+ * lengths of Sec. IV, e.g. 106 s at 40 Hz) with a known white PSD: the transform as a convolution
+ * (Bluestein) up to n = 8190, the band bins by their defining sum above.
  */
 typedef struct {
   int32_t n_det;        /* detector series */
@@ -143,7 +143,8 @@ typedef struct {
 /*
  * sft_make_sfts -- the SFTs and PSDs of every segment, asynchronously on hip_stream (returns
  * once the launch is enqueued; a device's first call for a segment length also builds that
- * length's twiddle tables, tens of KB, and keeps them on the device until the process ends).
+ * length's tables, tens of KB, up to 0.4 MB for a length that is no power of two, and keeps them on
+ * the device until the process ends).
  *   x    : DEVICE [n_det][n_total] strain series (FP64), read only.
  *   bins : DEVICE out [n_det][n_seg][n_bins][2] x~ = dt sum_j x_j e^{-2 pi i j k / n} of the band.
  *   psd  : DEVICE out [n_det][n_seg][n_bins] the estimated one-sided PSD.

@@ -2,7 +2,7 @@
 // Eq. d_SFT) with the per-SFT noise PSD estimate (bias-corrected running median of the SFT's
 // own periodogram), gaps detected as segments holding a non-finite sample.
 //
-// strain_sft_kernel: one workgroup per segment of n = 2M samples.  The real series is taken as
+// strain_sft_kernel: n a power of two.  One workgroup per segment of n = 2M samples.  The real series is taken as
 // M complex points z[m] = x[2m] + i x[2m+1], loaded in natural order into LDS and transformed
 // in place by radix-8 decimation-in-frequency passes (FP64); the n/2 + 1 bins of the real
 // transform follow from Z[k] and conj(Z[M - k]):
@@ -12,9 +12,11 @@
 // [0, n/2]), with B the mean of the middle order statistic of N unit exponentials.  The median
 // is the sorted block's middle element (ties broken by bin): found by a wavefront-wide sort of
 // the union of 64 neighbouring blocks (half widths w <= 32), or by rank counting per bin.
+// strain_blue_kernel, strain_dft_kernel: other even n with a known white PSD.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
+#include <complex>
 #include <cstdint>
 #include <map>
 #include <mutex>
@@ -488,7 +490,288 @@ __global__ __launch_bounds__(kStrainBlock) void strain_sft_kernel(
   if (tid == 0) keep[row] = 1;
 }
 
-// Segments whose length n is not a power of two: the band bins by their defining sum
+// ---------------------------------------------------------------------------- lengths that are no power of two
+// Bluestein's algorithm (L. I. Bluestein, IEEE Trans. Audio Electroacoust. 18, 451 (1970)): with
+// b[j] = e^{i pi j^2 / M} the M-point DFT of z (M = n / 2, packed as above) is
+//   Z[k] = conj(b[k]) sum_j (z[j] conj(b[j])) b[k - j],
+// a convolution, taken as a cyclic one of length L >= 2M - 1 by two L-point transforms in LDS.
+// L = R0 S with R0 in {8, 9, 10, 12} (16 for the largest) and S in {64, 128, 256, 512}: a first
+// pass of radix R0 and passes of radix 8 (2 or 4 for the leftover bits) over the R0 sub-transforms
+// of S points.  A power of two alone would take 8192 points where 4608 do (106 s at 40 Hz: M =
+// 2120), twice the LDS traffic and one workgroup per CU instead of two.
+//
+// Bound: LDS traffic.  Of the eight passes, the first reads the strain itself, the last of the
+// forward transform, the multiplication with the spectrum of b and the first of the inverse run
+// on the same points in registers: seven round trips of L points, ~1 MB per segment of 4240
+// samples, against 71 KB of strain and bins.  The inverse transform is the transposed (decimation
+// in time) flow on the conjugate, which takes the digit-reversed order the forward one leaves, so
+// nothing is reordered.  4396 segments of 4240 samples (129 h at 40 Hz, every bin): 0.27 ms, 1.36
+// TB/s of strain, bins and PSD, where the defining sum (strain_dft_kernel, 2.1e10 terms) takes
+// 11.9 ms.  One workgroup of nine wavefronts per CU (151 registers; held to 96 for two workgroups it
+// spills and takes 0.37 ms; half the threads with two points each 0.30 ms).
+template <int R0, int LOGS>
+struct BlueShape {
+  static constexpr int S = 1 << LOGS, L = R0 * S;
+  static constexpr int items = L / 8 > S ? L / 8 : S;
+  static constexpr int threads = (items + 63) / 64 * 64;
+};
+
+// e^{-2 pi i m / R} of the composite small transforms
+template <int R>
+struct Unit;
+template <>
+struct Unit<9> {
+  static constexpr double c[9] = {
+    1.00000000000000000000, 0.766044443118978035202, 0.173648177666930348852, -0.500000000000000000000,
+    -0.939692620785908384054, -0.939692620785908384054, -0.500000000000000000000, 0.173648177666930348852,
+    0.766044443118978035202};
+  static constexpr double s[9] = {
+    0.0, -0.642787609686539326323, -0.984807753012208059367, -0.866025403784438646764, -0.342020143325668733044,
+    0.342020143325668733044, 0.866025403784438646764, 0.984807753012208059367, 0.642787609686539326323};
+};
+template <>
+struct Unit<10> {
+  static constexpr double c[10] = {
+    1.00000000000000000000, 0.809016994374947424102, 0.309016994374947424102, -0.309016994374947424102,
+    -0.809016994374947424102, -1.00000000000000000000, -0.809016994374947424102, -0.309016994374947424102,
+    0.309016994374947424102, 0.809016994374947424102};
+  static constexpr double s[10] = {
+    0.0, -0.587785252292473129169, -0.951056516295153572116, -0.951056516295153572116, -0.587785252292473129169,
+    0.0, 0.587785252292473129169, 0.951056516295153572116, 0.951056516295153572116, 0.587785252292473129169};
+};
+template <>
+struct Unit<12> {
+  static constexpr double c[12] = {
+    1.00000000000000000000, 0.866025403784438646764, 0.500000000000000000000, 0.0, -0.500000000000000000000,
+    -0.866025403784438646764, -1.00000000000000000000, -0.866025403784438646764, -0.500000000000000000000, 0.0,
+    0.500000000000000000000, 0.866025403784438646764};
+  static constexpr double s[12] = {
+    0.0, -0.500000000000000000000, -0.866025403784438646764, -1.00000000000000000000, -0.866025403784438646764,
+    -0.500000000000000000000, 0.0, 0.500000000000000000000, 0.866025403784438646764, 1.00000000000000000000,
+    0.866025403784438646764, 0.500000000000000000000};
+};
+template <>
+struct Unit<16> {
+  static constexpr double c[16] = {
+    1.00000000000000000000, 0.923879532511286756128, 0.707106781186547524401, 0.382683432365089771728, 0.0,
+    -0.382683432365089771728, -0.707106781186547524401, -0.923879532511286756128, -1.00000000000000000000,
+    -0.923879532511286756128, -0.707106781186547524401, -0.382683432365089771728, 0.0, 0.382683432365089771728,
+    0.707106781186547524401, 0.923879532511286756128};
+  static constexpr double s[16] = {
+    0.0, -0.382683432365089771728, -0.707106781186547524401, -0.923879532511286756128, -1.00000000000000000000,
+    -0.923879532511286756128, -0.707106781186547524401, -0.382683432365089771728, 0.0, 0.382683432365089771728,
+    0.707106781186547524401, 0.923879532511286756128, 1.00000000000000000000, 0.923879532511286756128,
+    0.707106781186547524401, 0.382683432365089771728};
+};
+template <int R>
+__device__ inline double2 unit_root(int m)
+{
+  return make_double2(Unit<R>::c[m], Unit<R>::s[m]);
+}
+
+template <int R>
+__device__ inline void dft_any(double2* v);
+
+// R = A B points by B transforms of A points, the twiddles, and A transforms of B points
+template <int A, int B>
+__device__ inline void dft_ab(double2* v)
+{
+  double2 y[A * B];
+#pragma unroll
+  for (int n2 = 0; n2 < B; ++n2) {
+    double2 u[A];
+#pragma unroll
+    for (int n1 = 0; n1 < A; ++n1) u[n1] = v[B * n1 + n2];
+    dft_any<A>(u);
+#pragma unroll
+    for (int k1 = 0; k1 < A; ++k1) y[k1 * B + n2] = n2 * k1 == 0 ? u[k1] : cmul(u[k1], unit_root<A * B>(n2 * k1));
+  }
+#pragma unroll
+  for (int k1 = 0; k1 < A; ++k1) {
+    dft_any<B>(y + k1 * B);
+#pragma unroll
+    for (int k2 = 0; k2 < B; ++k2) v[k1 + A * k2] = y[k1 * B + k2];
+  }
+}
+
+template <int R>
+__device__ inline void dft_any(double2* v)
+{
+  if constexpr (R == 3) {
+    constexpr double s3 = 0.86602540378443864676;
+    const double2 t = cadd(v[1], v[2]), d = csub(v[1], v[2]);
+    const double2 m = make_double2(fma(-0.5, t.x, v[0].x), fma(-0.5, t.y, v[0].y));
+    v[0] = cadd(v[0], t);
+    v[1] = make_double2(fma(s3, d.y, m.x), fma(-s3, d.x, m.y));
+    v[2] = make_double2(fma(-s3, d.y, m.x), fma(s3, d.x, m.y));
+  } else if constexpr (R == 5) {
+    constexpr double c1 = 0.30901699437494742410, c2 = -0.80901699437494742410;
+    constexpr double s1 = 0.95105651629515357212, s2 = 0.58778525229247312917;
+    const double2 t1 = cadd(v[1], v[4]), t2 = cadd(v[2], v[3]), t3 = csub(v[1], v[4]), t4 = csub(v[2], v[3]);
+    const double2 m1 = make_double2(fma(c1, t1.x, fma(c2, t2.x, v[0].x)), fma(c1, t1.y, fma(c2, t2.y, v[0].y)));
+    const double2 m2 = make_double2(fma(c2, t1.x, fma(c1, t2.x, v[0].x)), fma(c2, t1.y, fma(c1, t2.y, v[0].y)));
+    const double2 q1 = make_double2(fma(s1, t3.x, s2 * t4.x), fma(s1, t3.y, s2 * t4.y));
+    const double2 q2 = make_double2(fma(s2, t3.x, -s1 * t4.x), fma(s2, t3.y, -s1 * t4.y));
+    v[0] = cadd(v[0], cadd(t1, t2));
+    v[1] = make_double2(m1.x + q1.y, m1.y - q1.x);
+    v[4] = make_double2(m1.x - q1.y, m1.y + q1.x);
+    v[2] = make_double2(m2.x + q2.y, m2.y - q2.x);
+    v[3] = make_double2(m2.x - q2.y, m2.y + q2.x);
+  } else if constexpr (R == 9) {
+    dft_ab<3, 3>(v);
+  } else if constexpr (R == 10) {
+    dft_ab<5, 2>(v);
+  } else if constexpr (R == 12) {
+    dft_ab<3, 4>(v);
+  } else if constexpr (R == 16) {
+    dft_ab<4, 4>(v);
+  } else {
+    dft_small<R>(v);
+  }
+}
+
+// Pass I over the S-point sub-transforms (FftShape<LOGS>): forward (decimation in frequency, as
+// fft_pass), or INV its transpose, which multiplies by the twiddles before the R-point DFT.  The
+// last forward pass has no twiddles; it multiplies by the spectrum of b, conjugates and goes on
+// with the transpose of itself.
+template <int R0, int LOGS, int I, bool INV>
+__device__ inline void blue_pass(double2* buf, const double2* __restrict__ ws, const double2* __restrict__ bh, int tid)
+{
+  using Sh = BlueShape<R0, LOGS>;
+  constexpr int LR = FftShape<LOGS>::lr(I), R = 1 << LR;
+  constexpr int LOGL = LOGS - 3 * I, LP = 1 << (LOGL - LR), N = Sh::L / R;
+#pragma unroll
+  for (int t0 = 0; t0 < N; t0 += Sh::threads) {
+    const int t = t0 + tid;
+    if (N % Sh::threads == 0 || t < N) {
+      const int n1 = t & (LP - 1);
+      const int base = ((t >> (LOGL - LR)) << LOGL) + n1;
+      double2 v[R];
+      if constexpr (LP == 1) {
+        double2 h[R];
+#pragma unroll
+        for (int k = 0; k < R; ++k) h[k] = bh[base + k];
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[k] = buf[swz(base + k)];
+        dft_small<R>(v);
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+          v[k] = cmul(v[k], h[k]);
+          v[k].y = -v[k].y;
+        }
+        dft_small<R>(v);
+      } else {
+        double2 wv[R];
+#pragma unroll
+        for (int k2 = 1; k2 < R; ++k2) wv[k2] = ws[(n1 * k2) << (LOGS - LOGL)];
+#pragma unroll
+        for (int k = 0; k < R; ++k) v[k] = buf[swz(base + LP * k)];
+        if constexpr (INV) {
+#pragma unroll
+          for (int k2 = 1; k2 < R; ++k2) v[k2] = cmul(v[k2], wv[k2]);
+        }
+        dft_small<R>(v);
+        if constexpr (!INV) {
+#pragma unroll
+          for (int k2 = 1; k2 < R; ++k2) v[k2] = cmul(v[k2], wv[k2]);
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < R; ++k) buf[swz(base + LP * k)] = v[k];
+    }
+  }
+  __syncthreads();
+  if constexpr (!INV && LP > 1) blue_pass<R0, LOGS, I + 1, false>(buf, ws, bh, tid);
+  else if constexpr (I > 0) blue_pass<R0, LOGS, I - 1, true>(buf, ws, bh, tid);
+}
+
+struct BlueTables {
+  const double2* b;     // [M] conj(b[j]) = e^{-i pi j^2 / M}
+  const double2* bh;    // [L] spectrum of b over L, in the order the forward transform leaves
+  const double2* wl;    // [L] e^{-2 pi i j / L}
+  const double2* ws;    // [S] e^{-2 pi i j / S}
+  const double2* rtw;   // [M/2 + 1] e^{-2 pi i k / n}
+};
+
+// One workgroup per segment; the PSD is the given white level (no estimate).
+template <int R0, int LOGS>
+__global__ __launch_bounds__((BlueShape<R0, LOGS>::threads)) void strain_blue_kernel(
+    const double* __restrict__ x, int64_t n_total, int32_t n_seg, int32_t M, double dt, double s_white, int32_t k_lo,
+    int32_t n_bins, BlueTables tt, double* __restrict__ bins, double* __restrict__ psd, int32_t* __restrict__ keep)
+{
+  using Sh = BlueShape<R0, LOGS>;
+  constexpr int S = Sh::S, NT = Sh::threads;
+  extern __shared__ double2 buf[];
+  __shared__ int s_bad;
+  const int row = blockIdx.x;
+  const int det = row / n_seg, seg = row - det * n_seg;
+  const double* xs = x + (int64_t)det * n_total + (int64_t)seg * 2 * M;
+  const int tid = threadIdx.x;
+  if (tid == 0) s_bad = 0;
+  __syncthreads();
+  bool bad = false;
+  if (tid < S) {
+    // z[j] conj(b[j]), zero from M on, through the radix-R0 pass
+    const bool al = (reinterpret_cast<uintptr_t>(xs) & 15) == 0;
+    const double2* xs2 = reinterpret_cast<const double2*>(xs);
+    double2 v[R0];
+#pragma unroll
+    for (int k = 0; k < R0; ++k) {
+      const int j = tid + S * k;
+      v[k] = make_double2(0.0, 0.0);
+      if (j < M) {
+        const double2 z = al ? xs2[j] : make_double2(xs[2 * j], xs[2 * j + 1]);
+        bad |= !(isfinite(z.x) && isfinite(z.y));
+        v[k] = cmul(z, tt.b[j]);
+      }
+    }
+    dft_any<R0>(v);
+#pragma unroll
+    for (int k = 0; k < R0; ++k) buf[swz(tid + S * k)] = k == 0 ? v[0] : cmul(v[k], tt.wl[tid * k]);
+  }
+  if (bad) s_bad = 1;
+  __syncthreads();
+  blue_pass<R0, LOGS, 0, false>(buf, tt.ws, tt.bh, tid);
+  if (tid < S) {
+    double2 v[R0];
+#pragma unroll
+    for (int k = 0; k < R0; ++k) v[k] = k == 0 ? buf[swz(tid)] : cmul(buf[swz(tid + S * k)], tt.wl[tid * k]);
+    dft_any<R0>(v);
+    // Z[j] = conj(b[j]) conj(v): each thread's points are its own, no barrier in between
+#pragma unroll
+    for (int k = 0; k < R0; ++k) {
+      const int j = tid + S * k;
+      if (j < M) buf[swz(j)] = cmul(tt.b[j], make_double2(v[k].x, -v[k].y));
+    }
+  }
+  __syncthreads();
+  double* bo = bins + (int64_t)row * 2 * n_bins;
+  double* po = psd + (int64_t)row * n_bins;
+  const bool gap = s_bad != 0;
+  // the bins of the real transform, as in strain_sft_kernel, pair (k, M - k) per thread
+  for (int k = tid; 2 * k <= M; k += NT) {
+    const int im = M - k - k_lo, ik = k - k_lo;
+    const bool wk = ik >= 0 && ik < n_bins, wm = 2 * k != M && im >= 0 && im < n_bins;
+    if (!wk && !wm) continue;
+    const double2 a = buf[swz(k)], b = buf[swz(k == 0 ? 0 : M - k)];
+    const double2 e = make_double2(0.5 * (a.x + b.x), 0.5 * (a.y - b.y));
+    const double2 o = make_double2(0.5 * (a.x - b.x), 0.5 * (a.y + b.y));
+    const double2 rt = tt.rtw[k];
+    const double2 ro = cmul(rt, o), ro2 = cmul(make_double2(-rt.x, rt.y), make_double2(-o.x, o.y));
+    if (wk) {
+      bo[2 * ik] = gap ? 0.0 : dt * (e.x + ro.y);
+      bo[2 * ik + 1] = gap ? 0.0 : dt * (e.y - ro.x);
+    }
+    if (wm) {
+      bo[2 * im] = gap ? 0.0 : dt * (e.x + ro2.y);
+      bo[2 * im + 1] = gap ? 0.0 : dt * (-e.y - ro2.x);
+    }
+  }
+  for (int i = tid; i < n_bins; i += NT) po[i] = gap ? 0.0 : s_white;
+  if (tid == 0) keep[row] = gap ? 0 : 1;
+}
+
+// Longer segments whose length is not a power of two: the band bins by their defining sum
 // X[k] = sum_j x_j e^{-2 pi i j k / n} (Eq. d_SFT), one bin per thread, the segment in LDS (read
 // as a broadcast), the twiddle advanced by the rotation e^{-2 pi i k / n} and re-anchored from
 // the exact table W[m] = e^{-2 pi i m / n} every kAnchor samples (rounding drift <= kAnchor eps).
@@ -556,15 +839,124 @@ __global__ __launch_bounds__(kStrainBlock) void strain_dft_kernel(
 
 static sft_status strain_fail(sft_status st, const char* msg) { return sft_set_error(st, msg); }
 
-// Twiddle tables of a segment length n, in long double rounded once to FP64: for n a power of
-// two, tw[j] = e^{-2 pi i j / M} (j < M/2, M = n/2) and rtw[k] = e^{-2 pi i k / n} (k <= M/2);
-// otherwise W[m] = e^{-2 pi i m / n} (m < n).  Built on a device's first call for n and kept
-// there until the process ends (tens of KB per length), so that later calls only launch.
+// Largest segment length of strain_blue_kernel: L = 8192 points (128 KiB of LDS) hold the n - 1 of the
+// convolution, and the next size does not fit the 160 KiB of a CU.  Above it, up to 16382 samples,
+// the defining sum (strain_dft_kernel).
+constexpr int kBlueMaxN = 8192;
+
+typedef void (*BlueFn)(const double*, int64_t, int32_t, int32_t, double, double, int32_t, int32_t, BlueTables, double*,
+                       double*, int32_t*);
+struct BlueSize {
+  int r0 = 0, logs = 0, threads = 0;
+  BlueFn fn = nullptr;
+  int S() const { return 1 << logs; }
+  int L() const { return r0 << logs; }
+};
+
+template <int R0, int LOGS>
+static void blue_offer(int need, BlueSize& best)
+{
+  using Sh = BlueShape<R0, LOGS>;
+  if (Sh::L < need || (best.fn && best.L() <= Sh::L)) return;
+  best.r0 = R0;
+  best.logs = LOGS;
+  best.threads = Sh::threads;
+  best.fn = strain_blue_kernel<R0, LOGS>;
+}
+
+template <int LOGS>
+static void blue_offer_s(int need, BlueSize& best)
+{
+  blue_offer<8, LOGS>(need, best);
+  blue_offer<9, LOGS>(need, best);
+  blue_offer<10, LOGS>(need, best);
+  blue_offer<12, LOGS>(need, best);
+}
+
+// the smallest transform that holds the convolution of n / 2 points
+static BlueSize blue_size(int n)
+{
+  BlueSize b;
+  blue_offer_s<6>(n - 1, b);
+  blue_offer_s<7>(n - 1, b);
+  blue_offer_s<8>(n - 1, b);
+  blue_offer_s<9>(n - 1, b);
+  blue_offer<16, 9>(n - 1, b);
+  return b;
+}
+
+// Tables of a segment length n, in long double rounded once to FP64: for n a power of two,
+// tw[j] = e^{-2 pi i j / M} (j < M/2, M = n/2) and rtw[k] = e^{-2 pi i k / n} (k <= M/2); for other
+// n up to kBlueMaxN the tables of strain_blue_kernel; above, W[m] = e^{-2 pi i m / n} (m < n).
+// Built on a device's first call for n and kept there until the process ends (tens of KB per
+// length, up to 0.4 MB for a length that is no power of two), so that later calls only launch.
 struct TwTables {
   double2* tw = nullptr;
   double2* rtw = nullptr;
   double2* W = nullptr;
+  double2* blue = nullptr;   // one block: b [M], bh [L], wl [L], ws [S], rtw [M/2 + 1]
 };
+
+typedef std::complex<long double> cld;
+static cld unit_ld(int64_t num, int64_t den)   // e^{-2 pi i num / den}
+{
+  const long double a = -2.0L * 3.141592653589793238462643383279502884L * (long double)(num % den) / (long double)den;
+  return cld(cosl(a), sinl(a));
+}
+
+// DFT of x[0], x[s], x[2 s], ... (m points) into y, by halving down to an odd length
+static void host_dft(const cld* x, int m, int s, cld* y)
+{
+  if (m % 2 == 0) {
+    const int h = m / 2;
+    host_dft(x, h, 2 * s, y);
+    host_dft(x + s, h, 2 * s, y + h);
+    for (int k = 0; k < h; ++k) {
+      const cld e = y[k], o = unit_ld(k, m) * y[h + k];
+      y[k] = e + o;
+      y[h + k] = e - o;
+    }
+    return;
+  }
+  for (int k = 0; k < m; ++k) {
+    cld t = 0;
+    for (int j = 0; j < m; ++j) t += x[(int64_t)j * s] * unit_ld((int64_t)j * k, m);
+    y[k] = t;
+  }
+}
+
+static std::vector<double2> blue_tables(int n, const BlueSize& z)
+{
+  const int M = n / 2, L = z.L(), S = z.S();
+  std::vector<double2> h;
+  h.reserve((size_t)M + 2 * L + S + M / 2 + 1);
+  auto put = [&](cld v) { h.push_back(make_double2((double)v.real(), (double)v.imag())); };
+  std::vector<cld> b(L, cld(0)), f(L);
+  for (int64_t j = 0; j < M; ++j) {
+    const cld c = unit_ld(j * j % n, n);   // e^{-i pi j^2 / M}
+    put(c);
+    b[j] = std::conj(c);
+    if (j > 0) b[L - j] = std::conj(c);
+  }
+  host_dft(b.data(), L, 1, f.data());
+  // position of output k of the forward transform: radix-R0 digit first, then the S-point order
+  std::vector<cld> r(L);
+  for (int k = 0; k < L; ++k) {
+    int q = k / z.r0, p = 0, len = S;
+    while (len > 1) {
+      const int rad = len >= 8 ? 8 : len;
+      len /= rad;
+      p += (q % rad) * len;
+      q /= rad;
+    }
+    r[(k % z.r0) * S + p] = f[k] / (long double)L;
+  }
+  for (const cld& v : r) put(v);
+  for (int j = 0; j < L; ++j) put(unit_ld(j, L));
+  for (int j = 0; j < S; ++j) put(unit_ld(j, S));
+  for (int k = 0; k <= M / 2; ++k) put(unit_ld(k, n));
+  return h;
+}
 
 static hipError_t upload(const std::vector<double2>& h, double2** d)
 {
@@ -592,7 +984,9 @@ static hipError_t twiddle_tables(int n, TwTables& out)
   }
   const long double pi = 3.141592653589793238462643383279502884L;
   TwTables t;
-  if ((n & (n - 1)) != 0) {
+  if ((n & (n - 1)) != 0 && n <= kBlueMaxN) {
+    e = upload(blue_tables(n, blue_size(n)), &t.blue);
+  } else if ((n & (n - 1)) != 0) {
     std::vector<double2> W(n);
     for (int m = 0; m < n; ++m) {
       const long double a = -2.0L * pi * (long double)m / (long double)n;
@@ -643,6 +1037,24 @@ extern "C" sft_status sft_make_sfts(const sft_strain_desc* d, const double* x, d
   TwTables tt;
   hipError_t e = twiddle_tables(n, tt);
   if (e != hipSuccess) return strain_fail(SFT_E_DEVICE, hipGetErrorString(e));
+  if (!pow2 && n <= kBlueMaxN) {
+    const BlueSize z = blue_size(n);
+    BlueTables bt;
+    bt.b = tt.blue;
+    bt.bh = bt.b + M;
+    bt.wl = bt.bh + z.L();
+    bt.ws = bt.wl + z.L();
+    bt.rtw = bt.ws + z.S();
+    const size_t lds = (size_t)z.L() * sizeof(double2);
+    if (lds > 65536) e = hipFuncSetAttribute((const void*)z.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e == hipSuccess && n_seg > 0) {
+      hipLaunchKernelGGL(z.fn, dim3((unsigned)(n_seg * d->n_det)), dim3(z.threads), lds, st, x, d->n_total, (int32_t)n_seg,
+                         M, d->dt, d->s_white, d->k_lo, d->n_bins, bt, bins, psd, keep);
+      e = hipGetLastError();
+    }
+    if (e != hipSuccess) return strain_fail(SFT_E_DEVICE, hipGetErrorString(e));
+    return SFT_OK;
+  }
   if (!pow2) {
     const size_t lds = (size_t)n * sizeof(double);
     if (lds > 65536)
