@@ -314,18 +314,23 @@ __global__ __launch_bounds__(256) void sum_planes_kernel(const float* __restrict
   if (wv == 0 && i < count) dst[i] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
 }
 
+__device__ inline void adam_update(float& p, float gi, float& m1, float& m2, float lr, float b1, float b2, float eps,
+                                   float c1, float c2)
+{
+  const float a = b1 * m1 + (1.f - b1) * gi;
+  const float v = b2 * m2 + (1.f - b2) * gi * gi;
+  m1 = a;
+  m2 = v;
+  p -= lr * (a / c1) / (sqrtf(v / c2) + eps);
+}
+
 __global__ void adam_kernel(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m1,
                             float* __restrict__ m2, int64_t count, float lr, float b1, float b2, float eps, float c1,
                             float c2)
 {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= count) return;
-  const float gi = g[i];
-  const float a = b1 * m1[i] + (1.f - b1) * gi;
-  const float v = b2 * m2[i] + (1.f - b2) * gi * gi;
-  m1[i] = a;
-  m2[i] = v;
-  p[i] -= lr * (a / c1) / (sqrtf(v / c2) + eps);
+  adam_update(p[i], g[i], m1[i], m2[i], lr, b1, b2, eps, c1, c2);
 }
 
 // inference epilogue on [2R][n] (rows 0..R-1 values, R..2R-1 tangents):
@@ -914,6 +919,462 @@ __device__ inline uint32_t feistel(uint32_t x, int h, uint32_t key)
   return (L << h) | R;
 }
 
+// row x of the source that position i of the shuffled order visits (h = 0: the given order)
+__device__ inline uint32_t shuffled_row(uint32_t i, uint32_t n, int h, uint32_t key)
+{
+  if (h == 0) return i;
+  uint32_t x = i;
+  do {
+    x = feistel(x, h, key);
+  } while (x >= n);
+  return x;
+}
+
+// ---------------------------------------------------------------------------- fused training step
+// Three launches per step for hidden widths 16 NT <= 128 (layer by layer: 23 launches, 252 us for a
+// batch of 4096 and 3 -> 128 x 4 -> 2, the GEMMs of 128 workgroups bound by the latency of their K
+// steps; here 38 us):
+//   train_rows_kernel  forward, loss and input gradients of 16 rows per workgroup;
+//   train_grad_kernel  every weight and bias gradient, in slices of the batch;
+//   train_step_kernel  the slices summed in order, Adam, and the loss.
+// Workspace of a batch padded to Bp rows (a multiple of 16; the padding has no gradient).
+struct StepBuf {
+  float* U;      // [Bp][3] the batch's inputs
+  float* Hs;     // [L][Bp][H] outputs of the hidden layers
+  float* Gs;     // [L][Bp][H] dL/dZ of the hidden layers
+  float* Go;     // [Bp][2] dL/dY
+  float* plane;  // [slices][P] gradients of the slices, packed as the parameters
+  double* part;  // [Bp / 16] loss partials
+  int64_t Bp;
+  int slices, slice_rows;
+};
+
+// Bound: the FP32 matrix cores (6 B H^2 flops a layer) and, at one workgroup per CU (4096 rows),
+// the chain of layers.  One wavefront per 16 output units: the workgroup's NT wavefronts hold the
+// layer's D = W^T h (units x 16 rows, v_mfma_f32_16x16x4f32: A[i][k] in lane i + 16 k, B[k][j] in
+// lane j + 16 k, D[i][j] in lane j + 16 (i / 4), element i % 4) and exchange the activations
+// through LDS, one barrier per layer.  K step s of lane group g takes input unit
+// 16 (s / 4) + 4 g + s % 4, so that a lane's four steps are one 16-byte LDS read and its four
+// outputs one 16-byte write.  The weights come straight from the parameters (L2), the next layer's
+// loads in flight during this one's products; the backward pass reads W along its rows (16 bytes a
+// load).  SiLU' of every layer waits in LDS for the backward pass.
+__device__ inline void silu_deriv(float z, float& h, float& d)
+{
+  // reciprocal from the hardware estimate and one Newton step (within an ulp of the quotient); the
+  // exponent is capped so that 1 + e^-z stays finite
+  const float e = 1.0f + expf(fminf(-z, 80.0f));
+  float s = __builtin_amdgcn_rcpf(e);
+  s = fmaf(s, fmaf(-e, s, 1.0f), s);
+  h = z * s;
+  d = s * (1.0f + z * (1.0f - s));
+}
+
+template <int NT>
+__global__ __launch_bounds__(64 * NT) void train_rows_kernel(const float* __restrict__ u, const float* __restrict__ y,
+                                                             uint32_t n, int64_t first, int64_t B, int64_t Bp, int h,
+                                                             uint32_t key, const float* __restrict__ par, int layers,
+                                                             float inv_b2, float* __restrict__ Ub,
+                                                             float* __restrict__ Hs, float* __restrict__ Gs,
+                                                             float* __restrict__ Go, double* __restrict__ part)
+{
+  constexpr int H = 16 * NT, HP = H + 4;
+  __shared__ float act[2][16 * HP];
+  __shared__ float red[NT][16][2];
+  extern __shared__ flt4m ds[];   // [layers][64 NT] SiLU'(Z) of this thread's units
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int ub = 16 * w + 4 * lk;   // this lane's output units ub .. ub + 3 of row li
+  const int64_t row = (int64_t)blockIdx.x * 16 + li;
+  const bool valid = row < B;
+  float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f, t0 = 0.0f, t1 = 0.0f;
+  if (valid) {
+    const int64_t x = shuffled_row((uint32_t)(first + row), n, h, key);
+    u0 = u[3 * x];
+    u1 = u[3 * x + 1];
+    u2 = u[3 * x + 2];
+    t0 = y[2 * x];
+    t1 = y[2 * x + 1];
+  }
+  if (w == 0 && lk == 0) {
+    Ub[3 * row] = u0;
+    Ub[3 * row + 1] = u1;
+    Ub[3 * row + 2] = u2;
+  }
+  float a[4 * NT], an[4 * NT];
+  auto load_fwd = [&](float* d, int l) {
+    const float* W = par + 4 * H + (int64_t)(l - 1) * (H * H + H) + 16 * w + li;
+#pragma unroll
+    for (int s = 0; s < 4 * NT; ++s) d[s] = W[(16 * (s >> 2) + 4 * lk + (s & 3)) * H];
+  };
+  auto load_bwd = [&](float* d, int l) {
+    const float* W = par + 4 * H + (int64_t)(l - 1) * (H * H + H) + (16 * w + li) * H + 4 * lk;
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      const flt4m v = *reinterpret_cast<const flt4m*>(W + 16 * q);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) d[4 * q + i] = v[i];
+    }
+  };
+  auto product = [&](const float* d, const float* in) {
+    flt4m c = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+      const flt4m b = *reinterpret_cast<const flt4m*>(in + li * HP + 16 * q + 4 * lk);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(d[4 * q + i], b[i], c, 0, 0, 0);
+    }
+    return c;
+  };
+  auto put = [&](float* lds, float* glb, int l, flt4m v) {
+    *reinterpret_cast<flt4m*>(lds + li * HP + ub) = v;
+    *reinterpret_cast<flt4m*>(glb + ((int64_t)l * Bp + row) * H + ub) = v;
+  };
+  if (layers > 1) load_fwd(a, 1);
+  flt4m hv, dv;
+  {
+    const flt4m w0 = *reinterpret_cast<const flt4m*>(par + ub), w1 = *reinterpret_cast<const flt4m*>(par + H + ub);
+    const flt4m w2 = *reinterpret_cast<const flt4m*>(par + 2 * H + ub), b = *reinterpret_cast<const flt4m*>(par + 3 * H + ub);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float hh, dd;
+      silu_deriv(fmaf(w2[v], u2, fmaf(w1[v], u1, w0[v] * u0)) + b[v], hh, dd);
+      hv[v] = hh;
+      dv[v] = dd;
+    }
+  }
+  ds[tid] = dv;
+  put(act[0], Hs, 0, hv);
+  int cur = 0;
+  __syncthreads();
+  for (int l = 1; l < layers; ++l) {
+    const flt4m b = *reinterpret_cast<const flt4m*>(par + 4 * H + (int64_t)(l - 1) * (H * H + H) + H * H + ub);
+    if (l + 1 < layers) load_fwd(an, l + 1);
+    else load_bwd(an, l);
+    const flt4m c = product(a, act[cur]);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      float hh, dd;
+      silu_deriv(c[v] + b[v], hh, dd);
+      hv[v] = hh;
+      dv[v] = dd;
+    }
+    ds[l * 64 * NT + tid] = dv;
+    cur ^= 1;
+    put(act[cur], Hs, l, hv);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 4 * NT; ++s) a[s] = an[s];
+  }
+  // output layer: W [H][2], the units' products summed over the lane groups, then the wavefronts
+  const float* Wo = par + 4 * H + (int64_t)(layers - 1) * (H * H + H);
+  const flt4m wa = *reinterpret_cast<const flt4m*>(Wo + 2 * ub), wb = *reinterpret_cast<const flt4m*>(Wo + 2 * ub + 4);
+  float y0 = hv[0] * wa[0], y1 = hv[0] * wa[1];
+  y0 = fmaf(hv[1], wa[2], y0);
+  y1 = fmaf(hv[1], wa[3], y1);
+  y0 = fmaf(hv[2], wb[0], y0);
+  y1 = fmaf(hv[2], wb[1], y1);
+  y0 = fmaf(hv[3], wb[2], y0);
+  y1 = fmaf(hv[3], wb[3], y1);
+  y0 += __shfl_xor(y0, 16);
+  y1 += __shfl_xor(y1, 16);
+  y0 += __shfl_xor(y0, 32);
+  y1 += __shfl_xor(y1, 32);
+  if (lk == 0) {
+    red[w][li][0] = y0;
+    red[w][li][1] = y1;
+  }
+  __syncthreads();
+  y0 = y1 = 0.0f;
+#pragma unroll
+  for (int i = 0; i < NT; ++i) {
+    y0 += red[i][li][0];
+    y1 += red[i][li][1];
+  }
+  const float r0 = valid ? y0 + Wo[2 * H] - t0 : 0.0f, r1 = valid ? y1 + Wo[2 * H + 1] - t1 : 0.0f;
+  const float g0 = r0 * inv_b2, g1 = r1 * inv_b2;
+  if (w == 0) {
+    if (lk == 0) {
+      Go[2 * row] = g0;
+      Go[2 * row + 1] = g1;
+    }
+    double sq = (double)r0 * (double)r0 + (double)r1 * (double)r1;   // the rows of lanes 0..15
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) sq += __shfl_xor(sq, o);
+    if (lane == 0) part[blockIdx.x] = sq;
+  }
+  flt4m gv;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const flt4m wv = v < 2 ? wa : wb;
+    gv[v] = fmaf(g1, wv[2 * (v & 1) + 1], g0 * wv[2 * (v & 1)]) * dv[v];
+  }
+  cur ^= 1;
+  put(act[cur], Gs, layers - 1, gv);
+  __syncthreads();
+  for (int l = layers - 1; l > 0; --l) {
+    if (l > 1) load_bwd(an, l - 1);
+    const flt4m c = product(a, act[cur]);
+    gv = c * ds[(l - 1) * 64 * NT + tid];
+    cur ^= 1;
+    put(act[cur], Gs, l - 1, gv);
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 4 * NT; ++s) a[s] = an[s];
+  }
+}
+
+// Gradients of one slice of the batch (blockIdx.y): workgroups of 64 x 64 tiles of the hidden
+// layers' dW = h^T G (and, in the first tile row, their bias gradients), then one for the first
+// layer and one for the output layer on the vector ALU.  Bound: the FP32 matrix cores and the reads
+// of h and G from L2.  Each wavefront takes a quarter of the slice's rows for the whole tile (16
+// products per 8 operand loads, and short FP32 chains: 15 steps of 4 rows for a slice of 240); the
+// four are summed in LDS in wavefront order.
+__global__ __launch_bounds__(256) void train_grad_kernel(StepBuf t, int H, int layers, int64_t P)
+{
+  __shared__ float red[4][32][68];
+  __shared__ float rb[4][64];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int li = lane & 15, lk = lane >> 4;
+  const int nt = (H + 63) / 64;
+  const int64_t r0 = (int64_t)blockIdx.y * t.slice_rows;
+  const int64_t r1 = r0 + t.slice_rows < t.Bp ? r0 + t.slice_rows : t.Bp;
+  float* out = t.plane + (int64_t)blockIdx.y * P;
+  const int tiles = (layers - 1) * nt * nt;
+  if ((int)blockIdx.x < tiles) {
+    const int l = 1 + (int)blockIdx.x / (nt * nt), q = (int)blockIdx.x % (nt * nt);
+    const int i0 = q / nt * 64, j0 = q % nt * 64;
+    const float* A = t.Hs + (int64_t)(l - 1) * t.Bp * H;
+    const float* G = t.Gs + (int64_t)l * t.Bp * H;
+    int ca[4], cb[4];   // columns past the width read column 0 and are not stored
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      ca[i] = i0 + 16 * i + li < H ? i0 + 16 * i + li : 0;
+      cb[i] = j0 + 16 * i + li < H ? j0 + 16 * i + li : 0;
+    }
+    flt4m acc[4][4];
+    float bs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = flt4m{0.0f, 0.0f, 0.0f, 0.0f};
+    const int64_t qr = t.slice_rows / 4;
+    const int64_t s0 = r0 + w * qr, s1 = s0 + qr < r1 ? s0 + qr : r1;
+    // chunks of 16 rows (a slice's quarter and the padded batch are multiples of 16), the next
+    // chunk's loads in flight during this one's products
+    float av[4][4], bv[4][4], an[4][4], bn[4][4];
+    auto load = [&](float (&x)[4][4], float (&g)[4][4], int64_t r) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          x[s][i] = A[(r + 4 * s + lk) * H + ca[i]];
+          g[s][i] = G[(r + 4 * s + lk) * H + cb[i]];
+        }
+    };
+    if (s0 < s1) load(av, bv, s0);
+    for (int64_t r = s0; r < s1; r += 16) {
+      load(an, bn, r + 16 < s1 ? r + 16 : r);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s][i], bv[s][j], acc[i][j], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bs[j] += bv[s][j];
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          av[s][i] = an[s][i];
+          bv[s][i] = bn[s][i];
+        }
+    }
+    out += 4 * (int64_t)H + (int64_t)(l - 1) * (H * H + H);
+    // two halves of 32 rows of the tile
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half) __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) red[w][16 * i + 4 * lk + v][16 * j + li] = acc[2 * half + i][j][v];
+      if (half == 0) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          bs[j] += __shfl_xor(bs[j], 16);
+          bs[j] += __shfl_xor(bs[j], 32);
+          if (lk == 0) rb[w][16 * j + li] = bs[j];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int i = 4 * e + w, gi = i0 + 32 * half + i, gj = j0 + lane;
+        if (gi < H && gj < H)
+          out[(int64_t)gi * H + gj] = ((red[0][i][lane] + red[1][i][lane]) + red[2][i][lane]) + red[3][i][lane];
+      }
+      if (half == 0 && i0 == 0 && w == 0 && j0 + lane < H)
+        out[(int64_t)H * H + j0 + lane] = ((rb[0][lane] + rb[1][lane]) + rb[2][lane]) + rb[3][lane];
+    }
+    return;
+  }
+  // first layer (3 inputs; the bias as an input of 1) or output layer (2 outputs): thread (unit c,
+  // row group k of nk), four interleaved partial sums per value, then the row groups in order
+  const bool first = (int)blockIdx.x == tiles;
+  const int nk = 256 / H, k = tid / H, c = tid % H;
+  float v[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[i][j] = 0.0f;
+  if (k < nk) {
+    const float* X = first ? t.Gs : t.Hs + (int64_t)(layers - 1) * t.Bp * H;
+    for (int64_t r = r0 + k; r < r1; r += 4 * nk) {
+      float xv[4], m[4][3];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int64_t rr = r + (int64_t)i * nk;
+        const bool in = rr < r1;
+        xv[i] = in ? X[rr * H + c] : 0.0f;
+        const float* mr = first ? t.U + 3 * rr : t.Go + 2 * rr;
+        m[i][0] = in ? mr[0] : 0.0f;
+        m[i][1] = in ? mr[1] : 0.0f;
+        m[i][2] = in && first ? mr[2] : 0.0f;
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        v[i][0] = fmaf(m[i][0], xv[i], v[i][0]);
+        v[i][1] = fmaf(m[i][1], xv[i], v[i][1]);
+        v[i][2] = first ? fmaf(m[i][2], xv[i], v[i][2]) : v[i][2] + m[i][0];
+        v[i][3] += first ? xv[i] : m[i][1];
+      }
+    }
+  }
+  float* rs = &red[0][0][0];   // [4][256]
+#pragma unroll
+  for (int j = 0; j < 4; ++j) rs[256 * j + tid] = (v[0][j] + v[1][j]) + (v[2][j] + v[3][j]);
+  __syncthreads();
+  if (k != 0) return;
+  float sum[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    sum[j] = rs[256 * j + c];
+    for (int i = 1; i < nk; ++i) sum[j] += rs[256 * j + i * H + c];
+  }
+  if (first) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) out[j * H + c] = sum[j];   // W [3][H], then b
+  } else {
+    out += 4 * (int64_t)H + (int64_t)(layers - 1) * (H * H + H);
+    out[2 * c] = sum[0];
+    out[2 * c + 1] = sum[1];
+    if (c < 2) out[2 * H + c] = sum[2 + c];
+  }
+}
+
+// One parameter per thread: the slices' gradients in order into grad, then (ADAM) the Adam step; the
+// last workgroup sums the loss partials.  Bound: the reads of the slices (3.6 MB for 18 slices of
+// 50306 parameters), all of a thread's in flight together.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void train_step_kernel(StepBuf t, int64_t P, double inv_b, float* __restrict__ grad,
+                                                         float* __restrict__ loss, float* __restrict__ p,
+                                                         float* __restrict__ m1, float* __restrict__ m2, float lr,
+                                                         float c1, float c2)
+{
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ double red[256];
+    double s = 0.0;
+    for (int64_t i = threadIdx.x; i < t.Bp / 16; i += 256) s += t.part[i];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int k = 128; k > 0; k >>= 1) {
+      if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) loss[0] = (float)(red[0] * inv_b);
+    return;
+  }
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= P) return;
+  // two chains over the even and the odd slices
+  float g0 = 0.0f, g1 = 0.0f;
+  int z = 0;
+#pragma unroll 8
+  for (; z + 1 < t.slices; z += 2) {
+    g0 += t.plane[(int64_t)z * P + i];
+    g1 += t.plane[(int64_t)(z + 1) * P + i];
+  }
+  if (z < t.slices) g0 += t.plane[(int64_t)z * P + i];
+  const float g = g0 + g1;
+  grad[i] = g;
+  if constexpr (ADAM) adam_update(p[i], g, m1[i], m2[i], lr, 0.9f, 0.999f, 1e-8f, c1, c2);
+}
+
+// widths of the fused step: one wavefront per 16 units, at most eight
+static bool train_fused_ok(int hidden) { return hidden % 16 == 0 && hidden >= 16 && hidden <= 128; }
+
+// Slices of the batch: about one workgroup of train_grad_kernel per CU (tiles per slice times
+// slices near 256), at least 64 rows each (a quarter per wavefront), at most 64 slices.
+static size_t step_layout(void* ws, int H, int L, int64_t P, int64_t B, StepBuf& t)
+{
+  const int nt = (H + 63) / 64, per = (L - 1) * nt * nt + 2;
+  t.Bp = (B + 15) / 16 * 16;
+  const int64_t want = std::min<int64_t>(64, std::max<int64_t>(1, std::min<int64_t>(256 / per, t.Bp / 64)));
+  t.slice_rows = (int)(((t.Bp + want - 1) / want + 63) / 64 * 64);
+  t.slices = (int)((t.Bp + t.slice_rows - 1) / t.slice_rows);
+  size_t off = 0;
+  auto take = [&](size_t bytes) {
+    char* q = (char*)ws + off;
+    off = (off + bytes + 255) / 256 * 256;
+    return q;
+  };
+  t.part = (double*)take((size_t)(t.Bp / 16) * sizeof(double));
+  t.U = (float*)take((size_t)t.Bp * 3 * sizeof(float));
+  t.Go = (float*)take((size_t)t.Bp * 2 * sizeof(float));
+  t.Hs = (float*)take((size_t)L * t.Bp * H * sizeof(float));
+  t.Gs = (float*)take((size_t)L * t.Bp * H * sizeof(float));
+  t.plane = (float*)take((size_t)t.slices * P * sizeof(float));
+  return off;
+}
+
+// Loss and gradient of rows first .. first + B - 1 of the (shuffled, h > 0) rows of u, y into loss
+// and s->grad; with adam, the Adam step too.
+static hipError_t train_step(sft_surrogate* s, const float* u, const float* y, int64_t n, int64_t first, int64_t B, int h,
+                             uint32_t key, float* loss, const StepBuf& t, bool adam, float lr, float c1, float c2,
+                             hipStream_t st)
+{
+  const int H = s->d.hidden, L = s->d.layers, NT = H / 16;
+  typedef void (*RowsFn)(const float*, const float*, uint32_t, int64_t, int64_t, int64_t, int, uint32_t, const float*, int,
+                         float, float*, float*, float*, float*, double*);
+  static const RowsFn rows_fn[8] = {train_rows_kernel<1>, train_rows_kernel<2>, train_rows_kernel<3>,
+                                    train_rows_kernel<4>, train_rows_kernel<5>, train_rows_kernel<6>,
+                                    train_rows_kernel<7>, train_rows_kernel<8>};
+  const RowsFn fn = rows_fn[NT - 1];
+  const size_t lds = (size_t)L * 64 * NT * sizeof(flt4m);
+  hipError_t e = hipSuccess;
+  if (lds > 32768) e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(fn, dim3((unsigned)(t.Bp / 16)), dim3(64 * NT), lds, st, u, y, (uint32_t)n, first, B, t.Bp, h, key,
+                     s->par, L, 2.0f / (float)B, t.U, t.Hs, t.Gs, t.Go, t.part);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const int nt = (H + 63) / 64;
+  hipLaunchKernelGGL(train_grad_kernel, dim3((unsigned)((L - 1) * nt * nt + 2), (unsigned)t.slices), dim3(256), 0, st, t, H,
+                     L, s->P);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (adam)
+    hipLaunchKernelGGL(train_step_kernel<true>, dim3(nblk(s->P) + 1), dim3(256), 0, st, t, s->P, 1.0 / (double)B, s->grad,
+                       loss, s->par, s->mom1, s->mom2, lr, c1, c2);
+  else
+    hipLaunchKernelGGL(train_step_kernel<false>, dim3(nblk(s->P) + 1), dim3(256), 0, st, t, s->P, 1.0 / (double)B, s->grad,
+                       loss, s->par, s->mom1, s->mom2, 0.0f, 1.0f, 1.0f);
+  return hipGetLastError();
+}
+
 // the rows first .. first + B - 1 of the shuffled order, copied into the batch buffers
 __global__ __launch_bounds__(256) void gather_batch_kernel(const float* __restrict__ u, const float* __restrict__ y,
                                                            uint32_t n, int64_t first, int64_t B, int h, uint32_t key,
@@ -921,10 +1382,7 @@ __global__ __launch_bounds__(256) void gather_batch_kernel(const float* __restri
 {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= B) return;
-  uint32_t x = (uint32_t)(first + r);
-  do {
-    x = feistel(x, h, key);
-  } while (x >= n);
+  const uint32_t x = shuffled_row((uint32_t)(first + r), n, h, key);
   ub[3 * r] = u[3 * (int64_t)x];
   ub[3 * r + 1] = u[3 * (int64_t)x + 1];
   ub[3 * r + 2] = u[3 * (int64_t)x + 2];
@@ -1039,12 +1497,20 @@ extern "C" sft_status sft_surrogate_loss_grad(sft_surrogate* s, const float* u, 
   if (n < 1 || n > (1 << 21)) return mlp_fail(SFT_E_RANGE, "sft_surrogate_loss_grad: n outside [1, 2^21]");
   hipStream_t st = (hipStream_t)hip_stream;
   const int splits = (int)std::min<int64_t>(64, std::max<int64_t>(1, n / 64));
+  const bool fused = train_fused_ok(s->d.hidden);
+  StepBuf sb;
   void* ws = nullptr;
-  hipError_t e = hipMallocAsync(&ws, train_bytes(s->d.hidden, s->d.layers, n, splits), st);
+  hipError_t e = hipMallocAsync(&ws, fused ? step_layout(nullptr, s->d.hidden, s->d.layers, s->P, n, sb)
+                                           : train_bytes(s->d.hidden, s->d.layers, n, splits), st);
   if (e != hipSuccess) return mlp_fail(SFT_E_NOMEM, "sft_surrogate_loss_grad", e);
-  TrainBuf t;
-  train_layout(ws, s->d.hidden, s->d.layers, n, splits, t);
-  e = loss_grad(s, u, y, n, loss, t, st);
+  if (fused) {
+    step_layout(ws, s->d.hidden, s->d.layers, s->P, n, sb);
+    e = train_step(s, u, y, n, 0, n, 0, 0u, loss, sb, false, 0.0f, 1.0f, 1.0f, st);
+  } else {
+    TrainBuf t;
+    train_layout(ws, s->d.hidden, s->d.layers, n, splits, t);
+    e = loss_grad(s, u, y, n, loss, t, st);
+  }
   if (e == hipSuccess && grad) e = hipMemcpyAsync(grad, s->grad, s->P * sizeof(float), hipMemcpyDeviceToDevice, st);
   hipError_t e2 = hipFreeAsync(ws, st);
   if (e != hipSuccess) return mlp_fail(SFT_E_DEVICE, "sft_surrogate_loss_grad", e);
@@ -1076,13 +1542,17 @@ extern "C" sft_status sft_surrogate_train(sft_surrogate* s, const float* u, cons
   const int64_t steps = n / batch;
   int h = 1;   // half width of the shuffling bijection: 2^(2h) >= n
   while (((int64_t)1 << (2 * h)) < n) ++h;
-  const size_t tb = train_bytes(s->d.hidden, s->d.layers, batch, splits);
+  const bool fused = train_fused_ok(s->d.hidden);
+  StepBuf sb;
+  const size_t tb = fused ? step_layout(nullptr, s->d.hidden, s->d.layers, s->P, batch, sb)
+                          : train_bytes(s->d.hidden, s->d.layers, batch, splits);
   void* ws = nullptr;
   float* dloss = nullptr;
   hipError_t e = hipMallocAsync(&ws, tb + steps * sizeof(float) + (size_t)batch * 5 * sizeof(float) + 256, st);
   if (e != hipSuccess) return mlp_fail(SFT_E_NOMEM, "sft_surrogate_train", e);
-  TrainBuf t;
-  train_layout(ws, s->d.hidden, s->d.layers, batch, splits, t);
+  TrainBuf t{};
+  if (fused) step_layout(ws, s->d.hidden, s->d.layers, s->P, batch, sb);
+  else train_layout(ws, s->d.hidden, s->d.layers, batch, splits, t);
   dloss = (float*)((char*)ws + tb);
   float* ub = (float*)((char*)ws + (tb + steps * sizeof(float) + 255) / 256 * 256);   // [batch][3]
   float* yb = ub + (size_t)batch * 3;                                                  // [batch][2]
@@ -1094,6 +1564,12 @@ extern "C" sft_status sft_surrogate_train(sft_surrogate* s, const float* u, cons
     for (int64_t k = 0; k < steps && e == hipSuccess; ++k, ++it) {
       // cosine learning-rate schedule from lr to lr_min
       const float lrt = lr_min + 0.5f * (lr - lr_min) * (1.0f + (float)cos(M_PI * (double)it / total));
+      if (fused) {
+        s->step += 1;
+        const float c1 = 1.0f - powf(0.9f, (float)s->step), c2 = 1.0f - powf(0.999f, (float)s->step);
+        e = train_step(s, u, y, n, k * batch, batch, h, key, dloss + k, sb, true, lrt, c1, c2, st);
+        continue;
+      }
       hipLaunchKernelGGL(gather_batch_kernel, dim3(nblk(batch)), dim3(256), 0, st, u, y, (uint32_t)n, k * batch,
                          (int64_t)batch, h, key, ub, yb);
       if ((e = hipGetLastError()) != hipSuccess) break;
