@@ -933,7 +933,7 @@ __device__ inline uint32_t shuffled_row(uint32_t i, uint32_t n, int h, uint32_t 
 // ---------------------------------------------------------------------------- fused training step
 // Three launches per step for hidden widths 16 NT <= 128 (layer by layer: 23 launches, 252 us for a
 // batch of 4096 and 3 -> 128 x 4 -> 2, the GEMMs of 128 workgroups bound by the latency of their K
-// steps; here 38 us):
+// steps; here 46 us):
 //   train_rows_kernel  forward, loss and input gradients of 16 rows per workgroup;
 //   train_grad_kernel  every weight and bias gradient, in slices of the batch;
 //   train_step_kernel  the slices summed in order, Adam, and the loss.
@@ -1127,7 +1127,7 @@ __global__ __launch_bounds__(64 * NT) void train_rows_kernel(const float* __rest
 // layers' dW = h^T G (and, in the first tile row, their bias gradients), then one for the first
 // layer and one for the output layer on the vector ALU.  Bound: the FP32 matrix cores and the reads
 // of h and G from L2.  Each wavefront takes a quarter of the slice's rows for the whole tile (16
-// products per 8 operand loads, and short FP32 chains: 15 steps of 4 rows for a slice of 240); the
+// products per 8 operand loads, and short FP32 chains: 4 steps of 4 rows for a slice of 64); the
 // four are summed in LDS in wavefront order.
 __global__ __launch_bounds__(256) void train_grad_kernel(StepBuf t, int H, int layers, int64_t P)
 {
@@ -1278,8 +1278,8 @@ __global__ __launch_bounds__(256) void train_grad_kernel(StepBuf t, int H, int l
 }
 
 // One parameter per thread: the slices' gradients in order into grad, then (ADAM) the Adam step; the
-// last workgroup sums the loss partials.  Bound: the reads of the slices (3.6 MB for 18 slices of
-// 50306 parameters), all of a thread's in flight together.
+// last workgroup sums the loss partials.  Bound: the reads of the slices (12.9 MB for 64 slices of
+// 50306 parameters), sixteen of a thread's in flight together.
 template <bool ADAM>
 __global__ __launch_bounds__(256) void train_step_kernel(StepBuf t, int64_t P, double inv_b, float* __restrict__ grad,
                                                          float* __restrict__ loss, float* __restrict__ p,
@@ -1318,13 +1318,15 @@ __global__ __launch_bounds__(256) void train_step_kernel(StepBuf t, int64_t P, d
 // widths of the fused step: one wavefront per 16 units, at most eight
 static bool train_fused_ok(int hidden) { return hidden % 16 == 0 && hidden >= 16 && hidden <= 128; }
 
-// Slices of the batch: about one workgroup of train_grad_kernel per CU (tiles per slice times
-// slices near 256), at least 64 rows each (a quarter per wavefront), at most 64 slices.
+// Slices of the batch: at least 64 rows each (a chunk of 16 per wavefront), at most 64 slices, about
+// 1024 workgroups of train_grad_kernel: four per CU hide the latency of the first loads better than
+// one with four chunks (32 steps of 4096 rows: 1.72 ms with 256 workgroups, 1.50 with 512, 1.47 with
+// 1024, the longer sum over the slices included).
 static size_t step_layout(void* ws, int H, int L, int64_t P, int64_t B, StepBuf& t)
 {
   const int nt = (H + 63) / 64, per = (L - 1) * nt * nt + 2;
   t.Bp = (B + 15) / 16 * 16;
-  const int64_t want = std::min<int64_t>(64, std::max<int64_t>(1, std::min<int64_t>(256 / per, t.Bp / 64)));
+  const int64_t want = std::min<int64_t>(64, std::max<int64_t>(1, std::min<int64_t>(1024 / per, t.Bp / 64)));
   t.slice_rows = (int)(((t.Bp + want - 1) / want + 63) / 64 * 64);
   t.slices = (int)((t.Bp + t.slice_rows - 1) / t.slice_rows);
   size_t off = 0;
