@@ -122,6 +122,23 @@ static void timing_slot(hipEvent_t* b, hipEvent_t* e)
 }
 
 // ============================================================================ data handle
+// Argument and result block of one sft_inner_product call (pinned host memory, which the kernels read
+// and write directly) with the device workspace of its scan.  A handle keeps up to kIpSlots of them
+// between calls, one per call in flight; a call beyond those makes its own and frees it.
+struct IpBlk {
+  double mc, q, tc, phic;
+  int32_t af, al;
+  double zp[2], zx[2], hhp, hhx, rho;
+  uint32_t fl;
+};
+struct IpSlot {
+  IpBlk* blk = nullptr;
+  void* ws = nullptr;
+  bool keep = false;   // on the data's device
+};
+static constexpr size_t kIpSlots = 4;
+static constexpr size_t kIpWsBytes = 256u << 10;   // 5000 chunks of 52 bytes; a scan cut finer allocates
+
 struct sft_data {
   int device;
   int32_t n_sft, n, k_lo, n_bins, storage;
@@ -140,7 +157,49 @@ struct sft_data {
   double* g_eph;          // [n_groups][9] detector r/c, v/c, a/c at the group's midpoint (Doppler), or null;
                           // set, every group holds one row
   double* row_tmid;       // [n_sft] midpoint t_start + T/2 of each row (bank ordering)
+  mutable std::mutex ip_mu;
+  mutable std::vector<IpSlot> ip_free;   // blocks of sft_inner_product not in use
 };
+
+static void ip_destroy(const IpSlot& s)
+{
+  if (s.blk) (void)hipHostFree(s.blk);
+  if (s.ws) (void)hipFree(s.ws);
+}
+
+static sft_status ip_acquire(const sft_data* d, IpSlot& s)
+{
+  s = IpSlot();
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  // kept blocks live on the data's device; called with another one current, the call makes its own
+  s.keep = e == hipSuccess && dev == d->device;
+  if (s.keep) {
+    std::lock_guard<std::mutex> lk(d->ip_mu);
+    if (!d->ip_free.empty()) {
+      s = d->ip_free.back();
+      d->ip_free.pop_back();
+      return SFT_OK;
+    }
+  }
+  if (e == hipSuccess) e = hipHostMalloc((void**)&s.blk, sizeof(IpBlk), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipMalloc(&s.ws, kIpWsBytes);
+  if (e == hipSuccess) return SFT_OK;
+  ip_destroy(s);
+  return fail(e == hipErrorOutOfMemory ? SFT_E_NOMEM : SFT_E_DEVICE, "sft_inner_product: %s", hipGetErrorString(e));
+}
+
+static void ip_release(const sft_data* d, const IpSlot& s)
+{
+  if (s.keep) {
+    std::lock_guard<std::mutex> lk(d->ip_mu);
+    if (d->ip_free.size() < kIpSlots) {
+      d->ip_free.push_back(s);
+      return;
+    }
+  }
+  ip_destroy(s);
+}
 
 template <typename Bin> __device__ inline void store_bin(Bin* p, double re, double im);
 template <> __device__ inline void store_bin<double2>(double2* p, double re, double im) { *p = make_double2(re, im); }
@@ -216,8 +275,7 @@ static void build_groups(const double* t_start, int32_t n_sft, double T, std::ve
 static sft_status load_device(const sft_data_desc* d, const double* t_start, const double* dx, const double* dp,
                               const double* fplus, const double* fcross, hipStream_t st, sft_data** out)
 {
-  sft_data* h = new sft_data();
-  std::memset(h, 0, sizeof(*h));
+  sft_data* h = new sft_data();   // value-initialised: null pointers
   HIP_OR_FAIL(hipGetDevice(&h->device));
   if (hipDeviceGetAttribute(&h->cu_count, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess ||
       h->cu_count < 1)
@@ -434,6 +492,7 @@ extern "C" void sft_free_data(sft_data* h)
   if (h->fx) (void)hipFree(h->fx);
   if (h->g_eph) (void)hipFree(h->g_eph);
   if (h->row_tmid) (void)hipFree(h->row_tmid);
+  for (const IpSlot& s : h->ip_free) ip_destroy(s);
   delete h;
 }
 
@@ -653,6 +712,17 @@ static ScanFn pick_kernel(const sft_data* d, const sft_opts* o, int wf, bool fs,
   return scan_pick_bf16(o->precision, kern, o->K, d->nd);
 }
 
+// The kernel of a bank of one template, or null where only the general one exists (the F-statistic,
+// Doppler and start forms, plain FP32 sums, BF16 storage, the chirp table).
+static ScanFn pick_one(const sft_data* d, const sft_opts* o, int wf, bool fs, bool dop)
+{
+  if (fs || dop || o->t_ref != SFT_REF_MID || wf == WF_TABLE || d->storage == SFT_STORE_BF16) return nullptr;
+  const int kern = o->kernel == SFT_KERNEL_DIRICHLET ? KERN_DIRICHLET : KERN_FRESNEL;
+  if (o->precision == SFT_PREC_FP64) return scan_pick_one_f64(wf, kern, o->K, d->nd);
+  if (o->precision == SFT_PREC_FP32_KAHAN) return scan_pick_one_f32(wf, kern, o->K, d->nd);
+  return nullptr;
+}
+
 __global__ void zero_counter_kernel(int32_t* c)
 {
   if (threadIdx.x == 0) c[0] = 0;
@@ -765,6 +835,14 @@ static void bind_bank(ScanArgs& a, const sft_bank& b)
   a.sky = b.sky;
 }
 
+static void layout_ws(Prepared& P)
+{
+  P.part_bytes = (size_t)P.a.n_chunks * P.nacc * P.n * sizeof(double);
+  P.flag_bytes = (size_t)P.a.n_chunks * P.n * sizeof(uint32_t);
+  P.counter_off = (P.part_bytes + P.flag_bytes + 255) / 256 * 256;
+  P.ws_bytes = P.counter_off + 256;
+}
+
 static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t n, const sft_opts* o,
                                const sft_tuning& t, Prepared& P, bool fs, int wf = -1, const double* wtab = nullptr,
                                const uint32_t* xflags = nullptr)
@@ -795,8 +873,13 @@ static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t 
   a.wtab = wtab;
   P.xflags = xflags;
   P.perm = nullptr;
-  P.fn = pick_kernel(d, o, wf >= 0 ? wf : o->waveform, fs, bank->sky != nullptr);
   P.nacc = fs ? 7 : 6;
+  P.n = n;
+  P.a_plus = o->a_plus;
+  P.a_cross = o->a_cross;
+  const int wfk = wf >= 0 ? wf : o->waveform;
+  const ScanFn one = n == 1 ? pick_one(d, o, wfk, fs, bank->sky != nullptr) : nullptr;
+  P.fn = pick_kernel(d, o, wfk, fs, bank->sky != nullptr);
   const int B = t.block ? t.block : 256;
   a.n_tiles = (int32_t)((n + B - 1) / B);
   int nb_cu = 0;
@@ -824,13 +907,16 @@ static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t 
   P.block = dim3(B);
   if (a.persistent) P.grid = dim3((unsigned)std::min<int64_t>(a.n_items, resident));
   else P.grid = dim3((unsigned)a.n_tiles, (unsigned)a.n_chunks);
-  P.part_bytes = (size_t)a.n_chunks * P.nacc * n * sizeof(double);
-  P.flag_bytes = (size_t)a.n_chunks * n * sizeof(uint32_t);
-  P.counter_off = (P.part_bytes + P.flag_bytes + 255) / 256 * 256;
-  P.ws_bytes = P.counter_off + 256;
-  P.n = n;
-  P.a_plus = o->a_plus;
-  P.a_cross = o->a_cross;
+  if (one) {
+    // one template: the same chunks, a timestamp group per lane, wavefront by wavefront over the chip
+    // (the sums do not depend on this)
+    const int per = a.chunk <= 64 ? 64 / a.chunk : 1;   // chunks per wavefront
+    P.fn = one;
+    P.block = dim3(64);
+    P.grid = dim3((unsigned)((a.n_chunks + per - 1) / per));
+    a.persistent = 0;
+  }
+  layout_ws(P);
   return SFT_OK;
 }
 
@@ -1298,20 +1384,25 @@ static sft_status surrogate_scan(const sft_data* d, const sft_bank* bank, int64_
   return SFT_OK;
 }
 
-extern "C" sft_status sft_template_bank_scan(const sft_data* d, const sft_bank* bank, int64_t n, const sft_opts* o,
-                                             sft_out* out, void* hip_stream)
+// The bank scan on st.  Its workspace is ws when that holds it (the inner product's own block), and
+// otherwise taken from the stream-ordered allocator.
+static sft_status scan_on(const sft_data* d, const sft_bank* bank, int64_t n, const sft_opts* o, sft_out* out,
+                          hipStream_t st, void* own, size_t own_bytes)
 {
   sft_status s = validate_scan(d, o);
   if (s != SFT_OK) return s;
   if ((s = validate_io(bank, n, out)) != SFT_OK || (s = validate_fstat(d, o, out)) != SFT_OK ||
       (s = validate_doppler(d, o, bank)) != SFT_OK || n == 0) return s;
-  hipStream_t st = (hipStream_t)hip_stream;
   if (o->waveform == SFT_WF_SURROGATE) return surrogate_scan(d, bank, n, o, out, st);
   Prepared P;
   if ((s = prepare_scan(d, bank, n, o, d->tune, P, out->twoF != nullptr)) != SFT_OK) return s;
   const bool track = d->tune.order == SFT_ORDER_TRACK && n > 1;
   BankOrder B;
   if (track && (s = order_layout(bank, n, B)) != SFT_OK) return s;
+  if (!track && P.ws_bytes <= own_bytes) {
+    const hipError_t eo = enqueue_scan(P, own, out, st, true);
+    return eo == hipSuccess ? SFT_OK : fail(SFT_E_DEVICE, "scan: launch failed: %s", hipGetErrorString(eo));
+  }
   void* ws = nullptr;
   HIP_OR_FAIL(hipMallocAsync(&ws, P.ws_bytes + (track ? B.bytes : 0), st));
   hipError_t e;
@@ -1326,6 +1417,12 @@ extern "C" sft_status sft_template_bank_scan(const sft_data* d, const sft_bank* 
   if (e != hipSuccess) return fail(SFT_E_DEVICE, "scan: launch failed: %s", hipGetErrorString(e));
   if (e2 != hipSuccess) return fail(SFT_E_DEVICE, "scan: hipFreeAsync: %s", hipGetErrorString(e2));
   return SFT_OK;
+}
+
+extern "C" sft_status sft_template_bank_scan(const sft_data* d, const sft_bank* bank, int64_t n, const sft_opts* o,
+                                             sft_out* out, void* hip_stream)
+{
+  return scan_on(d, bank, n, o, out, (hipStream_t)hip_stream, nullptr, 0);
 }
 
 // ---------------------------------------------------------------------------- allocation-free scan
@@ -1629,41 +1726,40 @@ extern "C" sft_status sft_inner_product(const sft_data* d, double mc, double q, 
 {
   sft_status s = validate_scan(d, o);
   if (s != SFT_OK) return s;
-  // one device block: 4 doubles in + 2 ints in, 7 doubles + 1 flag out
-  struct Blk {
-    double mc, q, tc, phic;
-    int32_t af, al;
-    double zp[2], zx[2], hhp, hhx, rho;
-    uint32_t fl;
-  };
-  Blk h{};
-  h.mc = mc;
-  h.q = q;
-  h.tc = t_c;
-  h.phic = phi_c;
-  h.af = a_first;
-  h.al = a_last;
-  Blk* dv = nullptr;
-  HIP_OR_FAIL(hipMalloc(&dv, sizeof(Blk)));
-  hipError_t e = hipMemcpy(dv, &h, sizeof(Blk), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    (void)hipFree(dv);
-    return fail(SFT_E_DEVICE, "sft_inner_product: %s", hipGetErrorString(e));
-  }
-  sft_bank b{&dv->mc, &dv->q, &dv->tc, &dv->phic, &dv->af, &dv->al};
-  sft_out ou{dv->zp, dv->zx, &dv->hhp, &dv->hhx, &dv->rho, &dv->fl};
-  s = sft_template_bank_scan(d, &b, 1, o, &ou, nullptr);
+  IpSlot slot;
+  if ((s = ip_acquire(d, slot)) != SFT_OK) return s;
+  IpBlk* b = slot.blk;
+  b->mc = mc;
+  b->q = q;
+  b->tc = t_c;
+  b->phic = phi_c;
+  b->af = a_first;
+  b->al = a_last;
+  sft_bank bank{};
+  bank.mc = &b->mc;
+  bank.q = &b->q;
+  bank.t_c = &b->tc;
+  bank.phi_c = &b->phic;
+  bank.a_first = &b->af;
+  bank.a_last = &b->al;
+  sft_out out{};
+  out.zp = b->zp;
+  out.zx = b->zx;
+  out.hhp = &b->hhp;
+  out.hhx = &b->hhx;
+  out.rho = &b->rho;
+  out.flags = &b->fl;
+  s = scan_on(d, &bank, 1, o, &out, nullptr, slot.ws, kIpWsBytes);
+  const hipError_t e = hipStreamSynchronize(nullptr);   // also after a failed launch: the block is reused
+  if (s == SFT_OK && e != hipSuccess) s = fail(SFT_E_DEVICE, "sft_inner_product: %s", hipGetErrorString(e));
   if (s == SFT_OK) {
-    e = hipMemcpy(&h, dv, sizeof(Blk), hipMemcpyDeviceToHost);  // waits for the default stream
-    if (e != hipSuccess) s = fail(SFT_E_DEVICE, "sft_inner_product: %s", hipGetErrorString(e));
+    if (zp) { zp[0] = b->zp[0]; zp[1] = b->zp[1]; }
+    if (zx) { zx[0] = b->zx[0]; zx[1] = b->zx[1]; }
+    if (hhp) *hhp = b->hhp;
+    if (hhx) *hhx = b->hhx;
+    if (rho) *rho = b->rho;
+    if (flags) *flags = b->fl;
   }
-  (void)hipFree(dv);
-  if (s != SFT_OK) return s;
-  if (zp) { zp[0] = h.zp[0]; zp[1] = h.zp[1]; }
-  if (zx) { zx[0] = h.zx[0]; zx[1] = h.zx[1]; }
-  if (hhp) *hhp = h.hhp;
-  if (hhx) *hhx = h.hhx;
-  if (rho) *rho = h.rho;
-  if (flags) *flags = h.fl;
-  return SFT_OK;
+  ip_release(d, slot);
+  return s;
 }

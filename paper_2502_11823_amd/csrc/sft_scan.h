@@ -144,9 +144,24 @@ __device__ inline void stage_window(Bin* sw, const Bin* const* rp, int sb, int w
 // a group (one per detector) share the SFT midpoint, hence the chirp, the window and
 // all 2K+1 kernel weights: those are evaluated once per group and contracted with the
 // bins of each of the ND rows (the projector Lambda carries the detector dependence).
-template <typename Bin, int PREC, int KERN, int KC, int ND, int WF, int FS, int DP, int REF>
-__device__ __forceinline__ void scan_item(const ScanArgs& a, const int K, const int64_t m, const int c, const float2* tab,
+// ONE: c is a group, sw the lane's slot of its seven terms (stride 64); returns the flag word.
+template <typename Bin, int PREC, int KERN, int KC, int ND, int WF, int FS, int DP, int REF, int ONE>
+__device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, const int64_t m, const int c, const float2* tab,
                                           Bin* sw);
+
+// ONE (a bank of one template): the lanes take timestamp groups instead of templates.  One lane of 64
+// working through its chunk leaves the chip waiting on one group's latency after another (73 us for
+// 4096 groups of 3 rows in chunks of 4, against 20 us at one group a lane).  The groups' terms go
+// to LDS, and one lane per chunk and sum adds them in group order, so that the sums are those of the
+// general kernel.  Lanes hold different rows, so the bins are gathered, and the series bounds are each
+// lane's own, which is what the wavefront of a single template uses.
+template <typename R>
+struct AccTerm {   // the one term of a lane's group
+  R s = 0;
+  __device__ inline void add(R x) { s = x; }
+  __device__ inline R get() const { return s; }
+};
+constexpr uint32_t kOneEntered = 1u << 31;   // the group entered the sums
 
 // Register budget: the FP32 Fresnel kernels with a compile-time window for groups of 2 or 3
 // rows, and the one-row K = 32 kernel, with the Newtonian chirp fit 96 VGPRs without
@@ -163,8 +178,9 @@ constexpr int scan_min_waves()
   return 1;
 }
 
-template <typename Bin, int PREC, int KERN, int KC, int ND, int WF, int FS = 0, int DP = 0, int REF = 0>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(scan_min_waves<PREC, KERN, KC, ND, WF>())))
+template <typename Bin, int PREC, int KERN, int KC, int ND, int WF, int FS = 0, int DP = 0, int REF = 0, int ONE = 0>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(ONE ? 1 : scan_min_waves<PREC, KERN, KC, ND, WF>())))
 void scan_kernel(ScanArgs a)
 {
   __shared__ float2 tab[SFT_G_NINT * (SFT_G_DEG + 1)];
@@ -175,9 +191,63 @@ void scan_kernel(ScanArgs a)
     __syncthreads();
   }
 
+  if constexpr (ONE != 0) {
+    using R = typename PrecTraits<PREC>::R;
+    using Acc = typename PrecTraits<PREC>::Acc;
+    __shared__ R sv[7][64];
+    __shared__ uint32_t sf[64];
+    const int lane = threadIdx.x, C = a.chunk;   // workgroups of one wavefront
+    const int Kw = KC >= 0 ? KC : a.K;
+    // the lane's group g (none: >= g_end) as a chunk of its own
+    auto terms = [&](int g, int g_end) {
+      uint32_t fl = 0;
+      if (g < g_end) fl = scan_item<Bin, PREC, KERN, KC, ND, WF, FS, DP, REF, ONE>(a, Kw, 0, g, tab, (Bin*)&sv[0][lane]);
+      sf[lane] = fl;
+    };
+    // sum q (0..5) or the flag word (6) over the lanes i0 .. i0 + n - 1, on from acc and fl
+    auto fold = [&](int q, int i0, int n, Acc& acc, uint32_t& fl) {
+      for (int i = i0; i < i0 + n; ++i) {
+        const uint32_t f = sf[i];
+        if (q < 6) {
+          if (f & kOneEntered) acc.add(sv[q][i]);
+        } else {
+          fl = ((fl | f) & ((1u << kUsedShift) - 1u)) | ((fl & ~((1u << kUsedShift) - 1u)) + (f & ~kOneEntered & ~((1u << kUsedShift) - 1u)));
+        }
+      }
+    };
+    auto write = [&](int c, int q, const Acc& acc, uint32_t fl) {
+      if (q < 6) a.part[(int64_t)c * 6 + q] = acc.get();
+      else a.pflags[c] = fl;
+    };
+    if (C <= 64) {
+      const int per = 64 / C, c0 = (int)blockIdx.x * per;   // chunks of this wavefront
+      terms(lane < per * C ? c0 * C + lane : a.n_groups, a.n_groups);
+      __syncthreads();
+      for (int t = lane; t < 8 * per; t += 64) {
+        const int q = t & 7, c = c0 + (t >> 3);
+        if (q > 6 || c >= a.n_chunks) continue;
+        Acc acc;
+        uint32_t fl = 0;
+        fold(q, (t >> 3) * C, C, acc, fl);
+        write(c, q, acc, fl);
+      }
+    } else {
+      const int c = (int)blockIdx.x, g0 = c * C, g1 = min(g0 + C, a.n_groups);
+      Acc acc;
+      uint32_t fl = 0;
+      for (int g = g0; g < g1; g += 64) {
+        terms(g + lane, g1);
+        __syncthreads();
+        if (lane < 7) fold(lane, 0, min(64, g1 - g), acc, fl);
+        __syncthreads();
+      }
+      if (lane < 7) write(c, lane, acc, fl);
+    }
+    return;
+  }
   __shared__ int s_item;
   // per wavefront (at most 4 per workgroup): the bins of the current timestamp group
-  constexpr int WST = stage_width<KC, WF>();
+  constexpr int WST = ONE ? 0 : stage_width<KC, WF>();
   __shared__ Bin stage[4 * ND * (WST > 0 ? WST : 1)];
   const int K = KC >= 0 ? KC : a.K;
   // A work item is (template tile, chunk of timestamp groups), chunk-major so that
@@ -197,21 +267,22 @@ void scan_kernel(ScanArgs a)
     const int c = item / a.n_tiles;
     const int64_t m = (int64_t)tile * blockDim.x + threadIdx.x;
     if (m < a.n_tmpl)
-      scan_item<Bin, PREC, KERN, KC, ND, WF, FS, DP, REF>(a, K, m, c, tab, stage + (threadIdx.x >> 6) * (ND * WST));
+      scan_item<Bin, PREC, KERN, KC, ND, WF, FS, DP, REF, ONE>(a, K, m, c, tab, stage + (threadIdx.x >> 6) * (ND * WST));
     if (!a.persistent) break;
   }
 }
 
-template <typename Bin, int PREC, int KERN, int KC, int ND, int WF, int FS, int DP, int REF>
-__device__ __forceinline__ void scan_item(const ScanArgs& a, const int K, const int64_t m, const int c, const float2* tab,
+// ONE: c is a group, sw the lane's slot of its seven terms (stride 64); returns the flag word.
+template <typename Bin, int PREC, int KERN, int KC, int ND, int WF, int FS, int DP, int REF, int ONE>
+__device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, const int64_t m, const int c, const float2* tab,
                                           Bin* sw)
 {
-  constexpr int WST = stage_width<KC, WF>();
+  constexpr int WST = ONE ? 0 : stage_width<KC, WF>();
   using R = typename PrecTraits<PREC>::R;
-  using Acc = typename PrecTraits<PREC>::Acc;
+  using Acc = typename std::conditional<ONE != 0, AccTerm<R>, typename PrecTraits<PREC>::Acc>::type;
   using PS = typename std::conditional<PREC == SFT_PREC_FP64, double, float>::type;
-  const int g0 = c * a.chunk;
-  const int g1 = min(g0 + a.chunk, a.n_groups) - 1;
+  const int g0 = ONE ? c : c * a.chunk;
+  const int g1 = ONE ? c : min(g0 + a.chunk, a.n_groups) - 1;
   const int lo = a.a_first ? (int)a.a_first[m] : 0;
   const int hi = a.a_last ? (int)a.a_last[m] : 0x7fffffff;
 
@@ -540,12 +611,14 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int K, const 
         auto dn = [&](float vt) {
           return -(int)fmaxf(fminf(floorf(fmaf(-vt, shb, dm)), -1.0f), (float)(-K - 1));
         };
-        jup = wave_max_active(up(SFT_G_VASYM), -K - 1, K + 1);
-        jdn = -wave_max_active(dn(SFT_G_VASYM), -K - 1, K + 1);
-        ju1 = wave_max_active(up(SFT_VASYM_W1), jup, K + 1);
-        jd1 = -wave_max_active(dn(SFT_VASYM_W1), -jdn, K + 1);
-        ju0 = wave_max_active(up(SFT_VASYM_W0), ju1, K + 1);
-        jd0 = -wave_max_active(dn(SFT_VASYM_W0), -jd1, K + 1);
+        // the wavefront's bound (one template per lane), or the lane's own
+        auto bound = [](int x, int lo, int hi) { return ONE ? x : wave_max_active(x, lo, hi); };
+        jup = bound(up(SFT_G_VASYM), -K - 1, K + 1);
+        jdn = -bound(dn(SFT_G_VASYM), -K - 1, K + 1);
+        ju1 = bound(up(SFT_VASYM_W1), jup, K + 1);
+        jd1 = -bound(dn(SFT_VASYM_W1), -jdn, K + 1);
+        ju0 = bound(up(SFT_VASYM_W0), ju1, K + 1);
+        jd0 = -bound(dn(SFT_VASYM_W0), -jd1, K + 1);
       }
       // E-+ / 2 pi with the imaginary parts of the beta < 0 mirror
       const float eqr = kInvTwoPiF * emr, eqy = kInvTwoPiF * (neg ? -emi : emi);
@@ -755,6 +828,7 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int K, const 
       ghx = fma(fxa * fxa, hterm, ghx);
       if constexpr (FS != 0) ghpx = fma(fpa * fxa, hterm, ghpx);
     }
+    if constexpr (ONE != 0) fl |= kOneEntered;
     zpr.add(gzpr);
     zpi.add(gzpi);
     zxr.add(gzxr);
@@ -764,6 +838,16 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int K, const 
     if constexpr (FS != 0) hpx.add(ghpx);
   }
 
+  if constexpr (ONE != 0) {
+    R* o = (R*)sw;
+    o[0] = zpr.get();
+    o[64] = zpi.get();
+    o[2 * 64] = zxr.get();
+    o[3 * 64] = zxi.get();
+    o[4 * 64] = hp.get();
+    o[5 * 64] = hx.get();
+    return fl;
+  }
   const int64_t n = a.n_tmpl;
   double* p = a.part + (int64_t)c * (6 + FS) * n + m;
   p[0] = zpr.get();
@@ -774,23 +858,24 @@ __device__ __forceinline__ void scan_item(const ScanArgs& a, const int K, const 
   p[5 * n] = hx.get();
   if constexpr (FS != 0) p[6 * n] = hpx.get();
   a.pflags[(int64_t)c * n + m] = fl;
+  return fl;
 }
 
 // ---------------------------------------------------------------------------- dispatch
 // Newtonian: every detector-group width 1..4.  3.5PN: widths 1 and 4 (groups of 2 or 3
 // rows run in the width-4 kernel, whose absent rows are skipped by a uniform test).
-template <typename Bin, int PREC, int KERN, int KC, int WF, int FS, int REF = 0>
+template <typename Bin, int PREC, int KERN, int KC, int WF, int FS, int REF = 0, int ONE = 0>
 static ScanFn pick_nd(int nd)
 {
   if constexpr (WF == WF_NEWTON) {
     switch (nd) {
-    case 1: return scan_kernel<Bin, PREC, KERN, KC, 1, WF, FS, 0, REF>;
-    case 2: return scan_kernel<Bin, PREC, KERN, KC, 2, WF, FS, 0, REF>;
-    case 3: return scan_kernel<Bin, PREC, KERN, KC, 3, WF, FS, 0, REF>;
-    default: return scan_kernel<Bin, PREC, KERN, KC, 4, WF, FS, 0, REF>;
+    case 1: return scan_kernel<Bin, PREC, KERN, KC, 1, WF, FS, 0, REF, ONE>;
+    case 2: return scan_kernel<Bin, PREC, KERN, KC, 2, WF, FS, 0, REF, ONE>;
+    case 3: return scan_kernel<Bin, PREC, KERN, KC, 3, WF, FS, 0, REF, ONE>;
+    default: return scan_kernel<Bin, PREC, KERN, KC, 4, WF, FS, 0, REF, ONE>;
     }
   } else {
-    return nd == 1 ? scan_kernel<Bin, PREC, KERN, KC, 1, WF, FS, 0, REF> : scan_kernel<Bin, PREC, KERN, KC, 4, WF, FS, 0, REF>;
+    return nd == 1 ? scan_kernel<Bin, PREC, KERN, KC, 1, WF, FS, 0, REF, ONE> : scan_kernel<Bin, PREC, KERN, KC, 4, WF, FS, 0, REF, ONE>;
   }
 }
 
@@ -806,25 +891,25 @@ static ScanFn pick_start(int kern, int nd)
 // FP64: the Dirichlet kernel with a compile-time window for K = 4 and a run-time one otherwise;
 // the FP64 Fresnel weights (a reference mode, dominated by their special functions) with the
 // run-time window only.
-template <typename Bin, int PREC, int KERN, int WF, int FS = 0>
+template <typename Bin, int PREC, int KERN, int WF, int FS = 0, int ONE = 0>
 static ScanFn pick_k(int K, int nd)
 {
   if constexpr (PREC == SFT_PREC_FP64) {
-    if constexpr (KERN == KERN_FRESNEL) return pick_nd<Bin, PREC, KERN, -1, WF, FS>(nd);
-    return K == 4 ? pick_nd<Bin, PREC, KERN, 4, WF, FS>(nd) : pick_nd<Bin, PREC, KERN, -1, WF, FS>(nd);
+    if constexpr (KERN == KERN_FRESNEL) return pick_nd<Bin, PREC, KERN, -1, WF, FS, 0, ONE>(nd);
+    return K == 4 ? pick_nd<Bin, PREC, KERN, 4, WF, FS, 0, ONE>(nd) : pick_nd<Bin, PREC, KERN, -1, WF, FS, 0, ONE>(nd);
   } else {
     // one-row Fresnel scans with K = 32 (space-like banks) get a compile-time window too
     if constexpr (KERN == KERN_FRESNEL && WF == WF_NEWTON)
-      if (K == 32 && nd == 1) return scan_kernel<Bin, PREC, KERN, 32, 1, WF, FS>;
-    return K == 8 ? pick_nd<Bin, PREC, KERN, 8, WF, FS>(nd) : pick_nd<Bin, PREC, KERN, -1, WF, FS>(nd);
+      if (K == 32 && nd == 1) return scan_kernel<Bin, PREC, KERN, 32, 1, WF, FS, 0, 0, ONE>;
+    return K == 8 ? pick_nd<Bin, PREC, KERN, 8, WF, FS, 0, ONE>(nd) : pick_nd<Bin, PREC, KERN, -1, WF, FS, 0, ONE>(nd);
   }
 }
 
-template <typename Bin, int PREC, int WF, int FS = 0>
+template <typename Bin, int PREC, int WF, int FS = 0, int ONE = 0>
 static ScanFn pick_kern(int kern, int K, int nd)
 {
-  return kern == KERN_DIRICHLET ? pick_k<Bin, PREC, KERN_DIRICHLET, WF, FS>(K, nd)
-                                : pick_k<Bin, PREC, KERN_FRESNEL, WF, FS>(K, nd);
+  return kern == KERN_DIRICHLET ? pick_k<Bin, PREC, KERN_DIRICHLET, WF, FS, ONE>(K, nd)
+                                : pick_k<Bin, PREC, KERN_FRESNEL, WF, FS, ONE>(K, nd);
 }
 
 // Doppler form: one row per timestamp group
