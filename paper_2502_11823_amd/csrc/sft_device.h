@@ -105,16 +105,22 @@ struct Chirp {
   double dres;   // fddot T^3 / 8 (bins): Taylor residual about the midpoint (Eq. max_tsft)
 };
 
-__device__ inline Chirp newton_chirp(double tau, double inv5M, double cf, double phi_c, double T)
+// y^(-1/8) for y > 0: FP32 estimate from the hardware log2/exp2 (about 1 ulp), two Newton steps
+__device__ inline double inv_root8(double y)
 {
-  double y = tau * inv5M;
-  float yf = (float)y;
-  // FP32 estimate from the hardware log2/exp2 (about 1 ulp); the Newton steps fix the rest
+  const float yf = (float)y;
   double s = (double)__builtin_amdgcn_exp2f(-0.125f * __builtin_amdgcn_logf(yf));
   for (int it = 0; it < 2; ++it) {
     double s2 = s * s, s4 = s2 * s2, s8 = s4 * s4;
     s = fma(s * 0.125, fma(-y, s8, 1.0), s);
   }
+  return s;
+}
+
+__device__ inline Chirp newton_chirp(double tau, double inv5M, double cf, double phi_c, double T)
+{
+  double y = tau * inv5M;
+  const double s = inv_root8(y);
   double s2 = s * s, s3 = s2 * s, s8 = (s2 * s2) * (s2 * s2);
   double itau = s8 * inv5M;
   Chirp c;
@@ -173,12 +179,7 @@ __device__ inline Chirp pn35_chirp(double tau, double nu, double inv5Mnu, double
                                    double phi_c, double T, const PNCoef& c)
 {
   const double th = tau * inv5Mnu;
-  const float thf = (float)th;
-  double s = (double)__builtin_amdgcn_exp2f(-0.125f * __builtin_amdgcn_logf(thf));
-  for (int it = 0; it < 2; ++it) {
-    const double s2 = s * s, s4 = s2 * s2, s8 = s4 * s4;
-    s = fma(s * 0.125, fma(-th, s8, 1.0), s);
-  }
+  const double s = inv_root8(th);
   const double L = log(th);
   const double s2 = s * s, s3 = s2 * s, s4 = s2 * s2, s5 = s4 * s, s6 = s4 * s2, s7 = s6 * s, s8 = s4 * s4;
   // phase bracket

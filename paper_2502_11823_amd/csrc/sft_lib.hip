@@ -1110,7 +1110,8 @@ __device__ inline PNMass pn_mass(double mc, double q, double tsun)
 __device__ inline void pn_head(const PNMass& pm, const PNCoef& c, double tau, double& ph, double& dph)
 {
   const double th = tau * pm.inv5Mnu;
-  const double t38 = pow(th, 0.375), t14 = pow(th, 0.25);
+  const double s = inv_root8(th), s2 = s * s, s4 = s2 * s2;
+  const double t38 = th * s4 * s, t14 = th * s4 * s2;   // Theta^(3/8), Theta^(1/4)
   ph = -2.0 / pm.nu * (c.p2 * t38 + c.p3 * t14);
   dph = -2.0 / pm.nu * (0.375 * c.p2 * t38 + 0.25 * c.p3 * t14) / th * pm.inv5Mnu;
 }
@@ -1179,25 +1180,30 @@ __device__ inline double psd_at(const PS* __restrict__ psd, int r, double kappa,
   return (1.0 - w) * S0 + w * S1;
 }
 
-// One lane per template of the batch: the surrogate chirp of every group the template
-// uses (Newtonian chirp plus the network's corrections), the judge against the 3.5PN
-// chirp, and the chirp table the scan reads (the 3.5PN chirps for a rejected template).
-// The judge's weight of SFT row r is A_PN^2 T / S_r(f_PN) (the row's share of <h,h>); rows
-// whose PSD is masked or outside the stored band at f_PN carry no weight.
+// The surrogate chirp of every (template, group) that is used (Newtonian chirp plus the network's
+// corrections), the judge against the 3.5PN chirp, and the chirp table the scan reads (the 3.5PN
+// chirps for a rejected template).  The judge's weight of SFT row r is A_PN^2 T / S_r(f_PN) (the
+// row's share of <h,h>); rows whose PSD is masked or outside the stored band at f_PN carry no weight.
+//
+// Bound: FP64 arithmetic of the two chirps.  A workgroup takes kPostT templates and spreads the groups
+// over kPostS slices (slice s takes the groups s, s + kPostS, ...; the judge's sums are combined over
+// the slices by a fixed tree in LDS).  One lane per template left half of the chip without work and
+// the rest with one wavefront per SIMD: 880 us for 32768 templates x 256 groups, 325 us so.
+constexpr int kPostT = 16, kPostS = 16;
+
 template <typename PS>
-__global__ __launch_bounds__(256) void sur_post_kernel(SurArgs sa, const double* __restrict__ mc,
-                                                       const double* __restrict__ q, const double* __restrict__ t_c,
-                                                       const double* __restrict__ phi_c, const int32_t* __restrict__ a_first,
-                                                       const int32_t* __restrict__ a_last,
-                                                       const double* __restrict__ g_tmid, const int32_t* __restrict__ g_rows,
-                                                       int64_t nb, int32_t n_groups, double T,
-                                                       const double* __restrict__ Y, const double* __restrict__ dY,
-                                                       double* __restrict__ tab, uint32_t* __restrict__ xflags,
-                                                       double* __restrict__ mismatch, const PS* __restrict__ psd,
-                                                       int32_t k_lo, int32_t n_bins)
+__global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
+    SurArgs sa, const double* __restrict__ mc, const double* __restrict__ q, const double* __restrict__ t_c,
+    const double* __restrict__ phi_c, const int32_t* __restrict__ a_first, const int32_t* __restrict__ a_last,
+    const double* __restrict__ g_tmid, const int32_t* __restrict__ g_rows, int64_t nb, int32_t n_groups, double T,
+    const double* __restrict__ Y, const double* __restrict__ dY, double* __restrict__ tab, uint32_t* __restrict__ xflags,
+    double* __restrict__ mismatch, const PS* __restrict__ psd, int32_t k_lo, int32_t n_bins)
 {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= nb) return;
+  __shared__ double red[3][kPostT * kPostS];
+  const int slice = threadIdx.x / kPostT;
+  const int64_t m_ = (int64_t)blockIdx.x * kPostT + threadIdx.x % kPostT;
+  const bool valid = m_ < nb;
+  const int64_t m = valid ? m_ : nb - 1;   // a lane past the end repeats the last template and stores nothing
   const int lo = a_first ? (int)a_first[m] : 0;
   const int hi = a_last ? (int)a_last[m] : 0x7fffffff;
   const double tc = t_c[m], phic = phi_c ? phi_c[m] : 0.0;
@@ -1208,19 +1214,31 @@ __global__ __launch_bounds__(256) void sur_post_kernel(SurArgs sa, const double*
   const PNCoef pc = pn_coefficients(pm.nu);
   const double dlt = 2.0 / sa.lt_span;   // du_tau / d ln tau
   const int64_t ps = (int64_t)n_groups * nb;
-  double sr = 0.0, si = 0.0, sw = 0.0;
-  for (int g = 0; g < n_groups; ++g) {
-    int n_act = 0;
+  auto used = [&](int g) {   // the template uses a row of group g
+    bool any = false;
     for (int d = 0; d < SFT_GROUP_MAX; ++d) {
       const int r = g_rows[g * SFT_GROUP_MAX + d];
-      n_act += (r >= 0 && r >= lo && r <= hi) ? 1 : 0;
+      any = any || (r >= 0 && r >= lo && r <= hi);
     }
+    return any;
+  };
+  auto store = [&](int g, const Chirp& c) {
+    double* w = tab + (int64_t)g * nb + m;
+    w[0] = c.kappa;
+    w[ps] = c.phase;
+    w[2 * ps] = c.amp;
+    w[3 * ps] = c.beta;
+    w[4 * ps] = c.dres;
+  };
+  double sr = 0.0, si = 0.0, sw = 0.0;
+  for (int g = slice; g < n_groups; g += kPostS) {
     const double tau = tc - g_tmid[g];
-    if (n_act == 0 || !(tau > 0.0)) continue;
+    if (!used(g) || !(tau > 0.0)) continue;
     const int64_t r = (int64_t)g * nb + m;
     const double y1 = Y[2 * r], y2 = Y[2 * r + 1], dy1 = dY[2 * r];
     const Chirp cn = newton_chirp(tau, inv5M, cf, phic, T);
-    const double Phi = pow(tau * inv5M, sa.p);
+    const double y = tau * inv5M, s = inv_root8(y), s2 = s * s, s4 = s2 * s2;
+    const double Phi = sa.head ? y * s4 * s2 * s : y * s4 * s;   // (tau / 5M)^p, p = 1/8 or 3/8
     double dphi = sa.c_phi * Phi * y1;
     double ddphi = sa.c_phi * Phi * (sa.p * y1 + dy1 * dlt) / tau;   // d(dphi)/dtau
     if (sa.head) {
@@ -1235,12 +1253,7 @@ __global__ __launch_bounds__(256) void sur_post_kernel(SurArgs sa, const double*
     cs.amp = cn.amp * exp(sa.c_amp * y2);
     cs.beta = cn.beta * pow(cs.kappa / cn.kappa, 11.0 / 3.0);
     cs.dres = (11.0 / 24.0) * cs.beta * cs.beta / cs.kappa;
-    double* w = tab + r;
-    w[0] = cs.kappa;
-    w[ps] = cs.phase;
-    w[2 * ps] = cs.amp;
-    w[3 * ps] = cs.beta;
-    w[4 * ps] = cs.dres;
+    if (valid) store(g, cs);
     // judge term: A_PN^2 T / S_r(f_PN) exp(i dphi) sinc(dkappa), summed over the group's rows
     const Chirp cp = pn35_chirp(tau, pm.nu, pm.inv5Mnu, pm.Mt, pm.nu25, phic, T, pc);
     const double dk = cs.kappa - cp.kappa;
@@ -1259,26 +1272,31 @@ __global__ __launch_bounds__(256) void sur_post_kernel(SurArgs sa, const double*
     si += wt * sd * snc;
     sw += wt;
   }
+  red[0][threadIdx.x] = sr;
+  red[1][threadIdx.x] = si;
+  red[2][threadIdx.x] = sw;
+  for (int h = kPostS / 2; h > 0; h >>= 1) {
+    __syncthreads();
+    if (slice < h)
+      for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + h * kPostT];
+  }
+  __syncthreads();
+  const int col = threadIdx.x % kPostT;
+  sr = red[0][col];
+  si = red[1][col];
+  sw = red[2][col];
   const double mm = sw > 0.0 ? 1.0 - sqrt(sr * sr + si * si) / sw : 0.0;
-  if (mismatch) mismatch[m] = mm;
   const bool fallback = !(mm <= sa.judge_tol);
-  xflags[m] = fallback ? kFlagSurrogateFallback : 0u;
+  if (!valid) return;
+  if (slice == 0) {
+    if (mismatch) mismatch[m] = mm;
+    xflags[m] = fallback ? kFlagSurrogateFallback : 0u;
+  }
   if (!fallback) return;
-  for (int g = 0; g < n_groups; ++g) {
-    int n_act = 0;
-    for (int d = 0; d < SFT_GROUP_MAX; ++d) {
-      const int r = g_rows[g * SFT_GROUP_MAX + d];
-      n_act += (r >= 0 && r >= lo && r <= hi) ? 1 : 0;
-    }
+  for (int g = slice; g < n_groups; g += kPostS) {
     const double tau = tc - g_tmid[g];
-    if (n_act == 0 || !(tau > 0.0)) continue;
-    const Chirp cp = pn35_chirp(tau, pm.nu, pm.inv5Mnu, pm.Mt, pm.nu25, phic, T, pc);
-    double* w = tab + (int64_t)g * nb + m;
-    w[0] = cp.kappa;
-    w[ps] = cp.phase;
-    w[2 * ps] = cp.amp;
-    w[3 * ps] = cp.beta;
-    w[4 * ps] = cp.dres;
+    if (!used(g) || !(tau > 0.0)) continue;
+    store(g, pn35_chirp(tau, pm.nu, pm.inv5Mnu, pm.Mt, pm.nu25, phic, T, pc));
   }
 }
 
@@ -1365,11 +1383,11 @@ static sft_status surrogate_scan(const sft_data* d, const sft_bank* bank, int64_
     if ((e = hipGetLastError()) != hipSuccess) break;
     if ((e = mlp_infer(sur, U, rows, Y, dY, ws + off_nn, chunk, st)) != hipSuccess) break;
     if (d->storage == SFT_STORE_F64)
-      hipLaunchKernelGGL(sur_post_kernel<double>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st, sa, b.mc, b.q,
+      hipLaunchKernelGGL(sur_post_kernel<double>, dim3((unsigned)((nb + kPostT - 1) / kPostT)), dim3(kPostT * kPostS), 0, st, sa, b.mc, b.q,
                          b.t_c, b.phi_c, b.a_first, b.a_last, d->g_tmid, d->g_rows, nb, d->n_groups, d->T, Y, dY, tab,
                          xf, ob.mismatch, (const double*)d->psd, d->k_lo, d->n_bins);
     else
-      hipLaunchKernelGGL(sur_post_kernel<float>, dim3((unsigned)((nb + 255) / 256)), dim3(256), 0, st, sa, b.mc, b.q,
+      hipLaunchKernelGGL(sur_post_kernel<float>, dim3((unsigned)((nb + kPostT - 1) / kPostT)), dim3(kPostT * kPostS), 0, st, sa, b.mc, b.q,
                          b.t_c, b.phi_c, b.a_first, b.a_last, d->g_tmid, d->g_rows, nb, d->n_groups, d->T, Y, dY, tab,
                          xf, ob.mismatch, (const float*)d->psd, d->k_lo, d->n_bins);
     if ((e = hipGetLastError()) != hipSuccess) break;
