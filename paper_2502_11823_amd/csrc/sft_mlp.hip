@@ -528,7 +528,9 @@ static hipError_t mlp_fused(const sft_surrogate* s, const double* U, int64_t n, 
 // significant bits) and each product takes three MFMAs, hi.hi + lo.hi + hi.lo (lo.lo is below
 // 2^-16 relative).  Without SPLIT: one MFMA of the rounded operands.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 typedef float flt4 __attribute__((ext_vector_type(4)));
+typedef float flt2 __attribute__((ext_vector_type(2)));
 
 static bool mlp_bf16_ok(int hidden) { return hidden % 32 == 0 && hidden >= 32 && hidden <= 128; }
 
@@ -575,180 +577,183 @@ __device__ inline void silu_tangent_f32(float z, float zt, float& h, float& t)
   t = s * (1.0f + z * (1.0f - s)) * zt;
 }
 
-// RT row tiles of 16 per wavefront (16 RT rows): each weight fragment read from LDS serves RT
-// tiles, and the fragments staged per workgroup serve 64 RT rows.  With split operands the
-// fragments are double buffered: layer l + 1's are loaded into LDS while layer l runs (the
-// layer's biases are read into registers before that prefetch is issued, so that waiting for
-// them does not wait for it).  The plain kernel keeps one buffer (its registers leave room for
-// two wavefronts per SIMD, which 128 KiB of LDS per workgroup would not).
-template <int NT, bool SPLIT, int RT>
-__global__ __launch_bounds__(256) void mlp_bf16_kernel(const double* __restrict__ U, int64_t n,
-                                                       const float* __restrict__ par,
-                                                       const bf16x8* __restrict__ frag, int layers,
-                                                       double* __restrict__ Y, double* __restrict__ dY)
+// elements e and e + 1 of a B operand: hi = bf16(x) and, SPLIT, lo = bf16(x - hi), two values per conversion
+template <bool SPLIT>
+__device__ inline void split_bf16(float x0, float x1, bf16x8& hi, bf16x8& lo, int e)
 {
-  constexpr int H = 16 * NT, S = H / 32;
-  constexpr int NF = NT * S * 2 * 64;   // fragments of one layer (a multiple of 256)
-  constexpr bool DB = SPLIT;
-  __shared__ bf16x8 wl2[(DB ? 2 : 1) * NF];
+  const flt2 x = {x0, x1};
+  const bf16x2v h = __builtin_convertvector(x, bf16x2v);
+  hi[e] = h[0];
+  hi[e + 1] = h[1];
+  if constexpr (SPLIT) {
+    const uint32_t w = __builtin_bit_cast(uint32_t, h);
+    const flt2 r = {x0 - __builtin_bit_cast(float, w << 16), x1 - __builtin_bit_cast(float, w & 0xffff0000u)};
+    const bf16x2v l = __builtin_convertvector(r, bf16x2v);
+    lo[e] = l[0];
+    lo[e + 1] = l[1];
+  }
+}
+
+// Bound: instruction issue.  A wavefront's 16 rows cost 192 MFMAs (4 issue cycles and 16 on the matrix cores
+// each) and 610 vector instructions a layer (SiLU with its derivative, 64 of the latter at a quarter rate, and
+// the split of the activations), so that the matrix cores wait unless other wavefronts of the SIMD fill in.
+// NW wavefronts per workgroup share the fragments in LDS: with split operands 12 of them (3 per SIMD within
+// 168 VGPRs, one workgroup of 128 KiB per CU), plain ones 8 (two workgroups per CU).  8.4 M rows of
+// 3 -> 128 x 4 -> 2, split: one wavefront per SIMD with 32 rows each 5.6 ms, 8 with 16 rows 4.8 ms, 12 4.5 ms.
+// The fragments are double buffered: layer l + 1's are loaded into LDS while layer l runs (the
+// layer's biases are read into registers before that prefetch is issued, so that waiting for
+// them does not wait for it).
+template <int NT, bool SPLIT, int NW>
+__global__ __launch_bounds__(64 * NW) void mlp_bf16_kernel(const double* __restrict__ U, int64_t n,
+                                                           const float* __restrict__ par,
+                                                           const bf16x8* __restrict__ frag, int layers,
+                                                           double* __restrict__ Y, double* __restrict__ dY)
+{
+  constexpr int H = 16 * NT, S = H / 32, P = SPLIT ? 2 : 1;
+  constexpr int NG = NT * S * P;        // groups of 64 fragments of one layer that are used
+  __shared__ bf16x8 wl2[2 * NG * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int j = lane & 15, g = lane >> 4;
-  const int64_t r0 = ((int64_t)blockIdx.x * 4 + wave) * 16 * RT + j;   // row of tile t: r0 + 16 t
+  const int64_t r = ((int64_t)blockIdx.x * NW + wave) * 16 + j;
   // direct global -> LDS copies of a layer's fragments: a wavefront fills 1 KiB at its
-  // wave-uniform base, lane i at base + 16 i
-  auto stage = [&](const bf16x8* F, bf16x8* dst) {
+  // wave-uniform base, lane i at base + 16 i (plain operands: the hi parts, every other group)
+  auto stage = [&](int l, bf16x8* dst) {
+    const bf16x8* F = frag + (int64_t)(l - 1) * (NT * S * 2 * 64);
 #pragma unroll
-    for (int c = 0; c < NF / 256; ++c)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(F + 256 * c + threadIdx.x),
-                                       (__attribute__((address_space(3))) void*)(dst + 256 * c + 64 * wave), 16, 0, 0);
+    for (int c = 0; c < (NG + NW - 1) / NW; ++c) {
+      const int i = NW * c + wave;
+      if (i < NG)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(F + (2 / P) * 64 * i + lane),
+                                         (__attribute__((address_space(3))) void*)(dst + 64 * i), 16, 0, 0);
+    }
   };
-  if (DB && layers > 1) stage(frag, wl2);   // layer 1, behind the first layer's work
-  float av[RT][NT][4], at[RT][NT][4];
+  if (layers > 1) stage(1, wl2);   // behind the first layer's work
+  float av[NT][4], at[NT][4];
   {
     const float* W = par;           // [3][H]
     const float* b = par + 3 * H;   // [H]
-#pragma unroll
-    for (int t = 0; t < RT; ++t) {
-      const int64_t r = r0 + 16 * t;
-      float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
-      if (r < n) {
-        u0 = (float)U[3 * r];
-        u1 = (float)U[3 * r + 1];
-        u2 = (float)U[3 * r + 2];
-      }
-#pragma unroll
-      for (int m = 0; m < NT; ++m)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int u = 16 * m + 4 * g + v;
-          const float z = fmaf(W[2 * H + u], u2, fmaf(W[H + u], u1, fmaf(W[u], u0, b[u])));
-          silu_tangent_f32(z, W[2 * H + u], av[t][m][v], at[t][m][v]);
-        }
+    float u0 = 0.0f, u1 = 0.0f, u2 = 0.0f;
+    if (r < n) {
+      u0 = (float)U[3 * r];
+      u1 = (float)U[3 * r + 1];
+      u2 = (float)U[3 * r + 2];
     }
-  }
-  int64_t off = 4 * H;
-  for (int l = 1; l < layers; ++l) {
-    // double buffer: this layer's fragments are in buffer (l - 1) % 2, and every wavefront is
-    // done with layer l - 1, whose buffer takes layer l + 1.  Single buffer: every wavefront is
-    // done with layer l - 1, and this layer's fragments are loaded now.
-    if constexpr (DB) __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    const bf16x8* wl = wl2 + (DB ? ((l - 1) & 1) * NF : 0);
-    float bl[NT][4];
-#pragma unroll
-    for (int mo = 0; mo < NT; ++mo)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) bl[mo][v] = par[off + H * H + 16 * mo + 4 * g + v];
-    if constexpr (DB) {
-      if (l + 1 < layers) stage(frag + (int64_t)l * NF, wl2 + (l & 1) * NF);
-    } else {
-      stage(frag + (int64_t)(l - 1) * NF, wl2);
-    }
-    // meanwhile the B operands of every K step: this lane's activations in the permuted order
-    bf16x8 bvh[RT][S], bvl[RT][S], bth[RT][S], btl[RT][S];
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-      for (int s = 0; s < S; ++s)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float x = av[t][2 * s + (e >> 2)][e & 3], y = at[t][2 * s + (e >> 2)][e & 3];
-          const __bf16 xh = (__bf16)x, yh = (__bf16)y;
-          bvh[t][s][e] = xh;
-          bth[t][s][e] = yh;
-          if constexpr (SPLIT) {
-            bvl[t][s][e] = (__bf16)(x - (float)xh);
-            btl[t][s][e] = (__bf16)(y - (float)yh);
-          }
-        }
-    if constexpr (!DB) {
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-    }
-#pragma unroll
-    for (int mo = 0; mo < NT; ++mo) {
-      flt4 cv[RT], ct[RT];
-#pragma unroll
-      for (int t = 0; t < RT; ++t) cv[t] = ct[t] = flt4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const bf16x8 ah = wl[((mo * S + s) * 2) * 64 + lane];
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-          cv[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bvh[t][s], cv[t], 0, 0, 0);
-          ct[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bth[t][s], ct[t], 0, 0, 0);
-        }
-        if constexpr (SPLIT) {
-          const bf16x8 al = wl[((mo * S + s) * 2 + 1) * 64 + lane];
-#pragma unroll
-          for (int t = 0; t < RT; ++t) {
-            cv[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bvh[t][s], cv[t], 0, 0, 0);
-            cv[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bvl[t][s], cv[t], 0, 0, 0);
-            ct[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bth[t][s], ct[t], 0, 0, 0);
-            ct[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, btl[t][s], ct[t], 0, 0, 0);
-          }
-        }
-      }
-      // the B operands hold this layer's inputs: the outputs may overwrite av, at
-#pragma unroll
-      for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          silu_tangent_f32(cv[t][v] + bl[mo][v], ct[t][v], av[t][mo][v], at[t][mo][v]);
-    }
-    off += (int64_t)H * H + H;
-  }
-  const float* W = par + off;   // [H][2]
-  const float* b = W + 2 * H;
-#pragma unroll
-  for (int t = 0; t < RT; ++t) {
-    float y0 = 0.0f, y1 = 0.0f, t0 = 0.0f, t1 = 0.0f;
 #pragma unroll
     for (int m = 0; m < NT; ++m)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int u = 16 * m + 4 * g + v;
-        y0 = fmaf(W[2 * u], av[t][m][v], y0);
-        y1 = fmaf(W[2 * u + 1], av[t][m][v], y1);
-        t0 = fmaf(W[2 * u], at[t][m][v], t0);
-        t1 = fmaf(W[2 * u + 1], at[t][m][v], t1);
+        const float z = fmaf(W[2 * H + u], u2, fmaf(W[H + u], u1, fmaf(W[u], u0, b[u])));
+        silu_tangent_f32(z, W[2 * H + u], av[m][v], at[m][v]);
       }
-    y0 += __shfl_xor(y0, 16);
-    y1 += __shfl_xor(y1, 16);
-    t0 += __shfl_xor(t0, 16);
-    t1 += __shfl_xor(t1, 16);
-    y0 += __shfl_xor(y0, 32);
-    y1 += __shfl_xor(y1, 32);
-    t0 += __shfl_xor(t0, 32);
-    t1 += __shfl_xor(t1, 32);
-    const int64_t r = r0 + 16 * t;
-    if (g == 0 && r < n) {
-      Y[2 * r] = (double)(y0 + b[0]);
-      Y[2 * r + 1] = (double)(y1 + b[1]);
-      dY[2 * r] = (double)t0;
-      dY[2 * r + 1] = (double)t1;
+  }
+  int64_t off = 4 * H;
+  for (int l = 1; l < layers; ++l) {
+    // this layer's fragments are in buffer (l - 1) % 2, and every wavefront is done with layer
+    // l - 1, whose buffer takes layer l + 1
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    const bf16x8* wl = wl2 + ((l - 1) & 1) * (NG * 64) + lane;
+    float bl[NT][4];
+#pragma unroll
+    for (int mo = 0; mo < NT; ++mo)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) bl[mo][v] = par[off + H * H + 16 * mo + 4 * g + v];
+    if (l + 1 < layers) stage(l + 1, wl2 + (l & 1) * (NG * 64));
+    // meanwhile the B operands of every K step: this lane's activations in the permuted order
+    bf16x8 bvh[S], bvl[S], bth[S], btl[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+      for (int e = 0; e < 8; e += 2) {
+        const int m = 2 * s + (e >> 2), v = e & 3;
+        split_bf16<SPLIT>(av[m][v], av[m][v + 1], bvh[s], bvl[s], e);
+        split_bf16<SPLIT>(at[m][v], at[m][v + 1], bth[s], btl[s], e);
+      }
+#pragma unroll
+    for (int mo = 0; mo < NT; ++mo) {
+      flt4 cv = flt4{0.0f, 0.0f, 0.0f, 0.0f}, ct = cv;
+#pragma unroll
+      for (int s = 0; s < S; ++s) {
+        const bf16x8 ah = wl[(mo * S + s) * P * 64];
+        cv = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bvh[s], cv, 0, 0, 0);
+        ct = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bth[s], ct, 0, 0, 0);
+        if constexpr (SPLIT) {
+          const bf16x8 al = wl[((mo * S + s) * P + 1) * 64];
+          cv = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bvh[s], cv, 0, 0, 0);
+          ct = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bth[s], ct, 0, 0, 0);
+          cv = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bvl[s], cv, 0, 0, 0);
+          ct = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, btl[s], ct, 0, 0, 0);
+        }
+      }
+      // the B operands hold this layer's inputs: the outputs may overwrite av, at
+#pragma unroll
+      for (int v = 0; v < 4; ++v) silu_tangent_f32(cv[v] + bl[mo][v], ct[v], av[mo][v], at[mo][v]);
     }
+    off += (int64_t)H * H + H;
+  }
+  const float* W = par + off;   // [H][2]
+  const float* b = W + 2 * H;
+  float y0 = 0.0f, y1 = 0.0f, t0 = 0.0f, t1 = 0.0f;
+#pragma unroll
+  for (int m = 0; m < NT; ++m)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int u = 16 * m + 4 * g + v;
+      y0 = fmaf(W[2 * u], av[m][v], y0);
+      y1 = fmaf(W[2 * u + 1], av[m][v], y1);
+      t0 = fmaf(W[2 * u], at[m][v], t0);
+      t1 = fmaf(W[2 * u + 1], at[m][v], t1);
+    }
+  y0 += __shfl_xor(y0, 16);
+  y1 += __shfl_xor(y1, 16);
+  t0 += __shfl_xor(t0, 16);
+  t1 += __shfl_xor(t1, 16);
+  y0 += __shfl_xor(y0, 32);
+  y1 += __shfl_xor(y1, 32);
+  t0 += __shfl_xor(t0, 32);
+  t1 += __shfl_xor(t1, 32);
+  if (g == 0 && r < n) {
+    Y[2 * r] = (double)(y0 + b[0]);
+    Y[2 * r + 1] = (double)(y1 + b[1]);
+    dY[2 * r] = (double)t0;
+    dY[2 * r + 1] = (double)t1;
   }
 }
 
-// rows per wavefront of the BF16 kernel: 16 * MLP_BF16_RT
-#ifndef MLP_BF16_RT
-#define MLP_BF16_RT 2
-#endif
+// Wavefronts per workgroup.  Widths below 128 take 8 (several workgroups share a CU: 64 units, 300 k rows, split
+// 50 us with 8 and 59 us with 12).  At 128 units a CU holds one workgroup, whose time is about 1.8 us times
+// 2.6 + its wavefronts (split, 3 hidden-to-hidden layers: 11.8, 18.6 and 26.4 us for 4, 8 and 12), so the size
+// with the least rounds x time over the 256 CUs is taken: 12 for large n, 8 for 50 k rows (37 us, 12: 53 us).
+template <int NT, bool SPLIT>
+static void mlp_bf16_go(const sft_surrogate* s, const double* U, int64_t n, double* Y, double* dY, hipStream_t st)
+{
+  const bf16x8* F = (const bf16x8*)s->frag;
+  const int L = s->d.layers;
+  int nw = 8;
+  if constexpr (NT == 8) {
+    auto cost = [&](int w) { return (double)((n + 4096 * w - 1) / (4096 * w)) * (2.6 + w); };
+    for (int w : {12, 4})
+      if (cost(w) < cost(nw)) nw = w;
+  }
+  const dim3 grid((unsigned)((n + 16 * nw - 1) / (16 * nw))), block(64 * nw);
+  void (*fn)(const double*, int64_t, const float*, const bf16x8*, int, double*, double*) = mlp_bf16_kernel<NT, SPLIT, 8>;
+  if constexpr (NT == 8) {
+    if (nw == 12) fn = mlp_bf16_kernel<NT, SPLIT, 12>;
+    if (nw == 4) fn = mlp_bf16_kernel<NT, SPLIT, 4>;
+  }
+  hipLaunchKernelGGL(fn, grid, block, 0, st, U, n, s->par, F, L, Y, dY);
+}
 
 template <bool SPLIT>
 static hipError_t mlp_bf16_launch(const sft_surrogate* s, const double* U, int64_t n, double* Y, double* dY,
                                   hipStream_t st)
 {
-  constexpr int RT = MLP_BF16_RT;
-  const dim3 grid((unsigned)((n + 64 * RT - 1) / (64 * RT))), block(256);
-  const int L = s->d.layers;
-  const bf16x8* F = (const bf16x8*)s->frag;
   switch (s->d.hidden / 32) {
-  case 1: hipLaunchKernelGGL((mlp_bf16_kernel<2, SPLIT, RT>), grid, block, 0, st, U, n, s->par, F, L, Y, dY); break;
-  case 2: hipLaunchKernelGGL((mlp_bf16_kernel<4, SPLIT, RT>), grid, block, 0, st, U, n, s->par, F, L, Y, dY); break;
-  case 3: hipLaunchKernelGGL((mlp_bf16_kernel<6, SPLIT, RT>), grid, block, 0, st, U, n, s->par, F, L, Y, dY); break;
-  default: hipLaunchKernelGGL((mlp_bf16_kernel<8, SPLIT, RT>), grid, block, 0, st, U, n, s->par, F, L, Y, dY); break;
+  case 1: mlp_bf16_go<2, SPLIT>(s, U, n, Y, dY, st); break;
+  case 2: mlp_bf16_go<4, SPLIT>(s, U, n, Y, dY, st); break;
+  case 3: mlp_bf16_go<6, SPLIT>(s, U, n, Y, dY, st); break;
+  default: mlp_bf16_go<8, SPLIT>(s, U, n, Y, dY, st); break;
   }
   return hipGetLastError();
 }
