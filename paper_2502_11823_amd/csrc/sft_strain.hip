@@ -11,7 +11,7 @@
 // block of N = 2w+1 periodogram values P[j] = |dt X[j]|^2 centred on k (shifted at the ends of
 // [0, n/2]), with B the mean of the middle order statistic of N unit exponentials.  The median
 // is the sorted block's middle element (ties broken by bin): found by a wavefront-wide sort of
-// the union of 64 neighbouring blocks (half widths w <= 32), or by rank counting per bin.
+// the union of 64 neighbouring blocks (half widths w <= 96), or by rank counting per bin.
 // strain_blue_kernel, strain_dft_kernel: other even n with a known white PSD.
 #include <hip/hip_runtime.h>
 
@@ -46,10 +46,14 @@ __device__ inline double2 cmul(double2 a, double2 b)
 // (value, bin) order, as a sort of the block itself gives.
 constexpr int kSortN = 128;
 constexpr int kMaxSortW = (kSortN - 64) / 2;   // w <= 32
-// LDS bytes of the sort slots of a workgroup: per wavefront the kSortN sorted values, then for
-// every position of the sorted list the 128-bit mask of the union bins (relative to the union's
-// first bin) that it and the entries before it hold
-constexpr int kSortBytes = kStrainBlock / 64 * kSortN * (int)(sizeof(double) + sizeof(uint4));
+constexpr int kMaxKeyW = (256 - 64) / 2;         // w <= 96: four 32-bit keys per lane (below)
+// LDS bytes of a wavefront's sort slot: the sorted list (64-bit values, or keys), then for every position of
+// the list the mask of the union bins (relative to the union's first bin) that it and the entries before
+// it hold
+__host__ __device__ constexpr int sort_slot(int w)
+{
+  return w <= kMaxSortW ? kSortN * (int)(sizeof(double) + sizeof(uint4)) : 256 * (4 + 32);
+}
 
 __device__ inline void wave_sync()
 {
@@ -146,6 +150,229 @@ __device__ inline void bitonic_from(double& a, int& ia, double& b, int& ib, int 
   bitonic_stage<SIZE, STRIDE>(a, ia, b, ib, lane);
   if constexpr (STRIDE > 1) bitonic_from<SIZE, STRIDE / 2>(a, ia, b, ib, lane);
   else if constexpr (SIZE < kSortN) bitonic_from<SIZE * 2, SIZE>(a, ia, b, ib, lane);
+}
+
+// ---- the same medians by a sort of 32-bit keys
+// The periodogram is positive, so the upper words of its values order them up to ties.  A key is the upper word
+// above the union's largest one minus R, in 32 - B bits, and the bin's place in the union in the B lowest (B = 7
+// or 8 for E = 2 or 4 keys per lane): ratios down to 2^-32 (2^-16) keep all 20 mantissa bits of the word, smaller
+// values share one key value.  A compare-exchange then is one lane exchange and one instruction instead of three
+// exchanges and a 64-bit compare with its selects.  The median found so is exact unless the entry beside it
+// in the sorted list has the same upper word (one chunk in thousands on noise): then the caller takes the
+// exact path for the whole chunk (the sort of pairs, or rank counting for w > 32).  12288 segments of 4096
+// samples, w = 25: 274 us with the pairs alone, 186 us so; 1000 of 1024 samples, w = 50: 510 us by rank
+// counting, 15 us so.
+template <int E>
+struct KeySort {
+  static constexpr int N = 64 * E, B = E == 2 ? 7 : 8;
+  static constexpr uint32_t R = (1u << (32 - B)) - 2;   // largest upper word of a key; the pads are above
+  static constexpr int kBytes = N * 4 + N * 8 * E;      // keys and prefix masks of a wavefront
+  uint32_t a[E];      // entry 64 e + lane of the list
+  uint32_t sm[6];     // all ones where bit s of the lane is set
+
+  // min (sel = 0) or max (sel = all ones) of x and y
+  static __device__ inline uint32_t pick(uint32_t x, uint32_t y, uint32_t sel)
+  {
+    const uint32_t lo = x < y ? x : y, hi = x < y ? y : x, m = hi < sel ? hi : sel;
+    return lo > m ? lo : m;
+  }
+  template <int SIZE, int STRIDE>
+  __device__ inline void stage()
+  {
+    if constexpr (STRIDE >= 64) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        if (e & (STRIDE / 64)) continue;
+        const uint32_t x = a[e], y = a[e + STRIDE / 64];
+        const bool up = ((64 * e) & SIZE) == 0;
+        a[e] = up ? min(x, y) : max(x, y);
+        a[e + STRIDE / 64] = up ? max(x, y) : min(x, y);
+      }
+    } else {
+      constexpr int LS = STRIDE == 1 ? 0 : STRIDE == 2 ? 1 : STRIDE == 4 ? 2 : STRIDE == 8 ? 3 : STRIDE == 16 ? 4 : 5;
+      constexpr int LZ = SIZE == 2 ? 1 : SIZE == 4 ? 2 : SIZE == 8 ? 3 : SIZE == 16 ? 4 : 5;
+      const uint32_t up = SIZE < 64 ? sm[LS] ^ sm[LZ] : sm[LS];
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const uint32_t sel = SIZE >= 64 && ((64 * e) & SIZE) ? ~up : up;
+        if constexpr (STRIDE == 32) {
+          const auto r = __builtin_amdgcn_permlane32_swap(a[e], a[e], false, false);   // both members of each pair
+          a[e] = pick(r[0], r[1], sel);
+        } else if constexpr (STRIDE == 16) {
+          const auto r = __builtin_amdgcn_permlane16_swap(a[e], a[e], false, false);
+          a[e] = pick(r[0], r[1], sel);
+        } else {
+          a[e] = pick(a[e], (uint32_t)lane_xor<STRIDE>((int)a[e], 0), sel);
+        }
+      }
+    }
+  }
+  template <int SIZE, int STRIDE>
+  __device__ inline void from()
+  {
+    stage<SIZE, STRIDE>();
+    if constexpr (STRIDE > 1) from<SIZE, STRIDE / 2>();
+    else if constexpr (SIZE < N) from<SIZE * 2, SIZE>();
+  }
+};
+
+static_assert(KeySort<2>::kBytes <= sort_slot(kMaxSortW) && KeySort<4>::kBytes <= sort_slot(kMaxKeyW), "sort slots");
+
+// largest value over the 64 lanes
+__device__ inline uint32_t wave_max(uint32_t x)
+{
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, true));    // row_shr:1
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, true));    // row_shr:2
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, true));    // row_shr:4
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, true));    // row_shr:8
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false));   // row_bcast:15
+  x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false));   // row_bcast:31
+  return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+
+// Medians of the blocks [s0r, s0r + 2w + 1) (one per lane, relative to u0) of the L values U[u0 ..]; slot holds
+// KeySort<E>::kBytes of the wavefront's LDS.  False (for the whole wavefront) where a lane of `want` needs
+// the exact path.
+template <int E>
+__device__ inline bool key_medians(const double* U, int u0, int L, int s0r, int w, int lane, bool want, char* slot,
+                                   double& med)
+{
+  using KS = KeySort<E>;
+  KS ks;
+  uint32_t top = 0, bot = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int p = 64 * e + lane;
+    const uint32_t h = p < L ? (uint32_t)((unsigned long long)__double_as_longlong(U[u0 + p]) >> 32) : 0;
+    ks.a[e] = h;
+    top = max(top, h);
+    bot = max(bot, p < L ? ~h : 0u);
+  }
+  top = wave_max(top);
+  bot = ~wave_max(bot);
+  // one key value for all, or an infinity or NaN
+  if (top == bot || top >= 0x7ff00000u) return false;
+  const uint32_t base = top > KS::R ? top - KS::R : 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int p = 64 * e + lane;
+    const uint32_t h = ks.a[e] > base ? ks.a[e] - base : 0;
+    ks.a[e] = p < L ? (h << KS::B) | (uint32_t)p : 0xffffffffu;
+  }
+#pragma unroll
+  for (int b = 0; b < 6; ++b) ks.sm[b] = (lane >> b) & 1 ? 0xffffffffu : 0u;
+  ks.template from<2, 1>();
+  // prefix masks of the sorted list: bit j of entry q is set when union bin j is one of the entries 0..q
+  uint32_t* keys = reinterpret_cast<uint32_t*>(slot);
+  uint4* pm = reinterpret_cast<uint4*>(slot + KS::N * 4);
+  uint32_t carry[2 * E] = {};
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const uint32_t id = ks.a[e] & (KS::N - 1);
+    const uint32_t bit = ks.a[e] == 0xffffffffu ? 0u : 1u << (id & 31);
+    uint32_t m[2 * E];
+#pragma unroll
+    for (int wd = 0; wd < 2 * E; ++wd) {
+      m[wd] = wave_or_scan((id >> 5) == (uint32_t)wd ? bit : 0u) | carry[wd];
+      carry[wd] = (uint32_t)__builtin_amdgcn_readlane((int)m[wd], 63);
+    }
+    keys[64 * e + lane] = ks.a[e];
+#pragma unroll
+    for (int h = 0; h < E / 2; ++h)
+      pm[(64 * e + lane) * (E / 2) + h] = make_uint4(m[4 * h], m[4 * h + 1], m[4 * h + 2], m[4 * h + 3]);
+  }
+  wave_sync();
+  // The count of a lane's block entries among the sorted entries 0..q is the popcount of pm[q] under the
+  // block's mask and grows with q; the block's median is the entry at which it reaches w + 1.
+  uint32_t wm[2 * E];
+#pragma unroll
+  for (int wd = 0; wd < 2 * E; ++wd) {
+    const int lo = min(max(s0r - 32 * wd, 0), 32), hi = min(max(s0r + 2 * w + 1 - 32 * wd, 0), 32);
+    wm[wd] = (uint32_t)(((1ull << hi) - 1ull) & ~((1ull << lo) - 1ull));
+  }
+  int qlo = 0, qhi = KS::N - 1;
+#pragma unroll
+  for (int it = 0; it < (E == 2 ? 7 : 8); ++it) {
+    const int mid = (qlo + qhi) >> 1;
+    int c = 0;
+#pragma unroll
+    for (int h = 0; h < E / 2; ++h) {
+      const uint4 p = pm[mid * (E / 2) + h];
+      c += __builtin_popcount(p.x & wm[4 * h]) + __builtin_popcount(p.y & wm[4 * h + 1]) +
+           __builtin_popcount(p.z & wm[4 * h + 2]) + __builtin_popcount(p.w & wm[4 * h + 3]);
+    }
+    if (c >= w + 1) qhi = mid;
+    else qlo = mid + 1;
+  }
+  const uint32_t kq = keys[qlo];
+  const uint32_t kp = qlo > 0 ? keys[qlo - 1] : 0xffffffffu, kn = qlo < KS::N - 1 ? keys[qlo + 1] : 0xffffffffu;
+  const bool tie = (kp >> KS::B) == (kq >> KS::B) || (kn >> KS::B) == (kq >> KS::B);
+  med = U[u0 + (int)(kq & (KS::N - 1))];
+  wave_sync();
+  return !__ballot(want && tie);
+}
+
+// The exact path: the medians by a sort of (value, bin) pairs, L <= kSortN.
+__device__ inline double pair_median(const double* U, int u0, int L, int s0r, int w, int lane, char* slot)
+{
+  double* sv = reinterpret_cast<double*>(slot);
+  uint4* pm = reinterpret_cast<uint4*>(slot + kSortN * 8);
+  const int N = 2 * w + 1;
+  // the kSortN pairs sorted in registers (two per lane), then stored in sorted order
+  double a = lane < L ? U[u0 + lane] : INFINITY, b = lane + 64 < L ? U[u0 + lane + 64] : INFINITY;
+  int ia = lane < L ? lane : 0x7fffffff, ib = lane + 64 < L ? lane + 64 : 0x7fffffff;
+  bitonic_from<2, 1>(a, ia, b, ib, lane);
+  // prefix masks of the sorted list: bit j of pm[q] is set when union bin j is one of the
+  // entries 0..q (an OR-scan of one-hot masks over the lanes, the second half of the list
+  // on top of the first; the pads set no bit)
+  uint32_t sa[4], sb[4];
+#pragma unroll
+  for (int wd = 0; wd < 4; ++wd) {
+    sa[wd] = wave_or_scan((ia >> 5) == wd ? 1u << (ia & 31) : 0u);
+    const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)sa[wd], 63);
+    sb[wd] = wave_or_scan((ib >> 5) == wd ? 1u << (ib & 31) : 0u) | t;
+  }
+  sv[lane] = a;
+  sv[lane + 64] = b;
+  pm[lane] = make_uint4(sa[0], sa[1], sa[2], sa[3]);
+  pm[lane + 64] = make_uint4(sb[0], sb[1], sb[2], sb[3]);
+  wave_sync();
+  // the smallest entry whose prefix holds w + 1 entries of the lane's block
+  uint32_t wm[4];
+#pragma unroll
+  for (int wd = 0; wd < 4; ++wd) {
+    const int lo = min(max(s0r - 32 * wd, 0), 32), hi = min(max(s0r + N - 32 * wd, 0), 32);
+    wm[wd] = (uint32_t)(((1ull << hi) - 1ull) & ~((1ull << lo) - 1ull));
+  }
+  int qlo = 0, qhi = kSortN - 1;
+#pragma unroll
+  for (int it = 0; it < 7; ++it) {
+    const int mid = (qlo + qhi) >> 1;
+    const uint4 p = pm[mid];
+    const int c = __builtin_popcount(p.x & wm[0]) + __builtin_popcount(p.y & wm[1]) +
+                  __builtin_popcount(p.z & wm[2]) + __builtin_popcount(p.w & wm[3]);
+    if (c >= w + 1) qhi = mid;
+    else qlo = mid + 1;
+  }
+  const double med = sv[qlo];
+  wave_sync();
+  return med;
+}
+
+// Median of the 2w + 1 values P by rank counting, ties broken by position.
+__device__ inline double rank_median(const double* P, int w)
+{
+  const int N = 2 * w + 1;
+  for (int a = 0; a < N; ++a) {
+    const double pa = P[a];
+    int rank = 0;
+    for (int b = 0; b < N; ++b) {
+      const double pb = P[b];
+      rank += (pb < pa || (pb == pa && b < a)) ? 1 : 0;
+    }
+    if (rank == w) return pa;
+  }
+  return 0.0;
 }
 
 // Transform of the M = 2^LOGM complex points in LDS (natural order in, digit-reversed out), as
@@ -395,16 +622,17 @@ __global__ __launch_bounds__(kStrainBlock) void strain_sft_kernel(
     if (tid == 0) keep[row] = 0;
     return;
   }
-  auto P = [&](int j) { return U[j]; };
   const int N = 2 * w + 1;
+  auto block_of = [&](int k) {   // first bin of the block centred on k, shifted at the ends of [0, M]
+    int s0 = k - w;
+    s0 = s0 < 0 ? 0 : s0;
+    return s0 + 2 * w > M ? M - 2 * w : s0;
+  };
   if (s_white > 0.0) {
     // a known white PSD: no estimate
     for (int i = tid; i < n_bins; i += blockDim.x) po[i] = s_white;
-  } else if (w <= kMaxSortW) {
+  } else if (w <= kMaxSortW || (LOGM >= 7 && w <= kMaxKeyW)) {
     const int lane = tid & 63, wv = tid >> 6;
-    double* sv = reinterpret_cast<double*>(reinterpret_cast<char*>(buf) + sort_off) + wv * kSortN;
-    uint4* pm = reinterpret_cast<uint4*>(reinterpret_cast<char*>(buf) + sort_off + (kStrainBlock / 64) * kSortN * 8) +
-                wv * kSortN;
     // every wavefront walks its chunks of 64 band bins (wave-uniform loop)
     for (int c0 = wv * 64; c0 < n_bins; c0 += blockDim.x) {
       const int kb = k_lo + c0;
@@ -414,78 +642,21 @@ __global__ __launch_bounds__(kStrainBlock) void strain_sft_kernel(
       int u1 = kb + 63 - w;
       u1 = u1 < 0 ? 0 : u1;
       u1 = u1 + 2 * w > M ? M - 2 * w : u1;
-      const int L = u1 + N - u0;                // <= 64 + 2w <= kSortN
-      // the kSortN pairs sorted in registers (two per lane), then stored in sorted order
-      double a = lane < L ? P(u0 + lane) : INFINITY, b = lane + 64 < L ? P(u0 + lane + 64) : INFINITY;
-      int ia = lane < L ? lane : 0x7fffffff, ib = lane + 64 < L ? lane + 64 : 0x7fffffff;
-      bitonic_from<2, 1>(a, ia, b, ib, lane);
-      // prefix masks of the sorted list: bit j of pm[q] is set when union bin j is one of the
-      // entries 0..q (an OR-scan of one-hot masks over the lanes, the second half of the list
-      // on top of the first; the pads set no bit)
-      uint32_t sa[4], sb[4];
-#pragma unroll
-      for (int wd = 0; wd < 4; ++wd) {
-        sa[wd] = wave_or_scan((ia >> 5) == wd ? 1u << (ia & 31) : 0u);
-        const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)sa[wd], 63);
-        sb[wd] = wave_or_scan((ib >> 5) == wd ? 1u << (ib & 31) : 0u) | t;
-      }
-      sv[lane] = a;
-      sv[lane + 64] = b;
-      pm[lane] = make_uint4(sa[0], sa[1], sa[2], sa[3]);
-      pm[lane + 64] = make_uint4(sb[0], sb[1], sb[2], sb[3]);
-      wave_sync();
-      // The count of a lane's block entries among the sorted entries 0..q is the popcount of
-      // pm[q] under the block's mask and grows with q; the block's median is the entry at which
-      // it reaches w + 1: the smallest such q, by a binary search (7 steps over kSortN).
+      const int L = u1 + N - u0;                // <= 64 + 2w
       const int i = c0 + lane;
-      const int k = k_lo + i;
-      int s0 = k - w;
-      s0 = s0 < 0 ? 0 : s0;
-      s0 = s0 + 2 * w > M ? M - 2 * w : s0;
-      const int s0r = s0 - u0;   // the block's first bin in the union
-      uint32_t wm[4];
-#pragma unroll
-      for (int wd = 0; wd < 4; ++wd) {
-        const int lo = min(max(s0r - 32 * wd, 0), 32), hi = min(max(s0r + N - 32 * wd, 0), 32);
-        wm[wd] = (uint32_t)(((1ull << hi) - 1ull) & ~((1ull << lo) - 1ull));
+      const int s0r = block_of(k_lo + i) - u0;  // the lane's block in the union
+      char* slot = reinterpret_cast<char*>(buf) + sort_off + wv * sort_slot(w);
+      double med = 0.0;
+      if (w <= kMaxSortW) {
+        if (!key_medians<2>(U, u0, L, s0r, w, lane, i < n_bins, slot, med)) med = pair_median(U, u0, L, s0r, w, lane, slot);
+      } else if constexpr (LOGM >= 7) {   // 2w <= M
+        if (!key_medians<4>(U, u0, L, s0r, w, lane, i < n_bins, slot, med) && i < n_bins) med = rank_median(U + u0 + s0r, w);
       }
-      int qlo = 0, qhi = kSortN - 1;
-#pragma unroll
-      for (int it = 0; it < 7; ++it) {
-        const int mid = (qlo + qhi) >> 1;
-        const uint4 p = pm[mid];
-        const int c = __builtin_popcount(p.x & wm[0]) + __builtin_popcount(p.y & wm[1]) +
-                      __builtin_popcount(p.z & wm[2]) + __builtin_popcount(p.w & wm[3]);
-        if (c >= w + 1) qhi = mid;
-        else qlo = mid + 1;
-      }
-      const int mq = qlo;
-      const double med = sv[mq];
       if (i < n_bins) po[i] = psd_scale * (dt * dt) * med;
-      wave_sync();
     }
   } else {
-    // wide blocks: rank counting per bin (ties broken by position)
-    for (int i = tid; i < n_bins; i += blockDim.x) {
-      const int k = k_lo + i;
-      int s0 = k - w;
-      s0 = s0 < 0 ? 0 : s0;
-      s0 = s0 + 2 * w > M ? M - 2 * w : s0;
-      double med = 0.0;
-      for (int a = 0; a < N; ++a) {
-        const double pa = P(s0 + a);
-        int rank = 0;
-        for (int b = 0; b < N; ++b) {
-          const double pb = P(s0 + b);
-          rank += (pb < pa || (pb == pa && b < a)) ? 1 : 0;
-        }
-        if (rank == w) {
-          med = pa;
-          break;
-        }
-      }
-      po[i] = psd_scale * (dt * dt) * med;
-    }
+    for (int i = tid; i < n_bins; i += blockDim.x)
+      po[i] = psd_scale * (dt * dt) * rank_median(U + block_of(k_lo + i), w);
   }
   if (tid == 0) keep[row] = 1;
 }
@@ -1080,9 +1251,9 @@ extern "C" sft_status sft_make_sfts(const sft_strain_desc* d, const double* x, d
   size_t lds = (size_t)M * sizeof(double2);
   int32_t sort_off = 0;
   int32_t flag_off = (int32_t)(((size_t)(M + 1) * sizeof(double) + 15) / 16 * 16);
-  if (!(d->s_white > 0.0) && d->psd_w <= kMaxSortW) {
+  if (!(d->s_white > 0.0) && d->psd_w <= kMaxKeyW) {
     sort_off = flag_off;
-    flag_off = sort_off + kSortBytes;
+    flag_off = sort_off + kStrainBlock / 64 * sort_slot(d->psd_w);
   }
   if ((size_t)flag_off + 16 > lds) lds = (size_t)flag_off + 16;
   const void* kern = nullptr;
