@@ -676,15 +676,21 @@ __global__ __launch_bounds__(kStrainBlock) void strain_sft_kernel(
 // on the same points in registers: seven round trips of L points, ~1 MB per segment of 4240
 // samples, against 71 KB of strain and bins.  The inverse transform is the transposed (decimation
 // in time) flow on the conjugate, which takes the digit-reversed order the forward one leaves, so
-// nothing is reordered.  4396 segments of 4240 samples (129 h at 40 Hz, every bin): 0.27 ms, 1.36
-// TB/s of strain, bins and PSD, where the defining sum (strain_dft_kernel, 2.1e10 terms) takes
-// 11.9 ms.  One workgroup of nine wavefronts per CU (151 registers; held to 96 for two workgroups it
-// spills and takes 0.37 ms; half the threads with two points each 0.30 ms).
+// nothing is reordered.  One workgroup of nine wavefronts per CU (162 registers; held to 96 for two
+// workgroups it spills) cannot hide what the passes wait for, so a thread reads one root per pass at the
+// start and forms the twiddles as its powers, and the spectrum of b a pass ahead.  4396 segments of 4240
+// samples (129 h at 40 Hz, every bin): 11.9 ms by the defining sum (strain_dft_kernel, 2.1e10 terms), 0.27 ms
+// with every twiddle read where it is used, 0.22 ms so (1.7 TB/s of strain, bins and PSD).
 template <int R0, int LOGS>
 struct BlueShape {
   static constexpr int S = 1 << LOGS, L = R0 * S;
   static constexpr int items = L / 8 > S ? L / 8 : S;
   static constexpr int threads = (items + 63) / 64 * 64;
+  // The last pass's operand is read a pass ahead where that pass has one work item per thread and the
+  // registers do not cost a wavefront per SIMD: S = 512 up to 12 wavefronts (one workgroup per CU), not
+  // S = 64 (20 k segments of 602 samples: 114 us with it, 109 us without).
+  static constexpr int last = 1 << FftShape<LOGS>::lr(FftShape<LOGS>::NP - 1);   // its radix
+  static constexpr bool ahead = LOGS == 9 && L / last <= threads && threads <= 768;
 };
 
 // e^{-2 pi i m / R} of the composite small transforms
@@ -801,16 +807,34 @@ __device__ inline void dft_any(double2* v)
   }
 }
 
+// The powers w, w^2 .. w^(R-1) of a root, each from the two halves of its exponent (at most three products deep)
+template <int R>
+__device__ inline void powers(double2 w, double2* p)
+{
+  p[1] = w;
+#pragma unroll
+  for (int k = 2; k < R; ++k) p[k] = cmul(p[k / 2], p[k - k / 2]);
+}
+
 // Pass I over the S-point sub-transforms (FftShape<LOGS>): forward (decimation in frequency, as
 // fft_pass), or INV its transpose, which multiplies by the twiddles before the R-point DFT.  The
 // last forward pass has no twiddles; it multiplies by the spectrum of b, conjugates and goes on
-// with the transpose of itself.
+// with the transpose of itself.  A work item's twiddles are powers of one root per pass, which the
+// kernel reads at its start (wp[I]); the spectrum of b (h) is read a pass ahead.
 template <int R0, int LOGS, int I, bool INV>
-__device__ inline void blue_pass(double2* buf, const double2* __restrict__ ws, const double2* __restrict__ bh, int tid)
+__device__ inline void blue_pass(double2* buf, const double2* wp, const double2* __restrict__ bh, double2* h, int tid)
 {
   using Sh = BlueShape<R0, LOGS>;
-  constexpr int LR = FftShape<LOGS>::lr(I), R = 1 << LR;
+  using Ff = FftShape<LOGS>;
+  constexpr int LR = Ff::lr(I), R = 1 << LR;
   constexpr int LOGL = LOGS - 3 * I, LP = 1 << (LOGL - LR), N = Sh::L / R;
+  // the pass before the last reads the spectrum of b for it
+  if constexpr (!INV && I == Ff::NP - 2 && Sh::ahead) {
+    if (Sh::L / Sh::last == Sh::threads || tid < Sh::L / Sh::last) {
+#pragma unroll
+      for (int k = 0; k < Sh::last; ++k) h[k] = bh[tid * Sh::last + k];
+    }
+  }
 #pragma unroll
   for (int t0 = 0; t0 < N; t0 += Sh::threads) {
     const int t = t0 + tid;
@@ -818,12 +842,13 @@ __device__ inline void blue_pass(double2* buf, const double2* __restrict__ ws, c
       const int n1 = t & (LP - 1);
       const int base = ((t >> (LOGL - LR)) << LOGL) + n1;
       double2 v[R];
+#pragma unroll
+      for (int k = 0; k < R; ++k) v[k] = buf[swz(base + LP * k)];
       if constexpr (LP == 1) {
-        double2 h[R];
+        if constexpr (!Sh::ahead) {
 #pragma unroll
-        for (int k = 0; k < R; ++k) h[k] = bh[base + k];
-#pragma unroll
-        for (int k = 0; k < R; ++k) v[k] = buf[swz(base + k)];
+          for (int k = 0; k < R; ++k) h[k] = bh[base + k];
+        }
         dft_small<R>(v);
 #pragma unroll
         for (int k = 0; k < R; ++k) {
@@ -833,10 +858,7 @@ __device__ inline void blue_pass(double2* buf, const double2* __restrict__ ws, c
         dft_small<R>(v);
       } else {
         double2 wv[R];
-#pragma unroll
-        for (int k2 = 1; k2 < R; ++k2) wv[k2] = ws[(n1 * k2) << (LOGS - LOGL)];
-#pragma unroll
-        for (int k = 0; k < R; ++k) v[k] = buf[swz(base + LP * k)];
+        powers<R>(wp[I], wv);   // t and t0 + tid have the same n1: threads is a multiple of LP
         if constexpr (INV) {
 #pragma unroll
           for (int k2 = 1; k2 < R; ++k2) v[k2] = cmul(v[k2], wv[k2]);
@@ -852,8 +874,20 @@ __device__ inline void blue_pass(double2* buf, const double2* __restrict__ ws, c
     }
   }
   __syncthreads();
-  if constexpr (!INV && LP > 1) blue_pass<R0, LOGS, I + 1, false>(buf, ws, bh, tid);
-  else if constexpr (I > 0) blue_pass<R0, LOGS, I - 1, true>(buf, ws, bh, tid);
+  if constexpr (!INV && LP > 1) blue_pass<R0, LOGS, I + 1, false>(buf, wp, bh, h, tid);
+  else if constexpr (I > 0) blue_pass<R0, LOGS, I - 1, true>(buf, wp, bh, h, tid);
+}
+
+// Root of a work item of pass I: W_{2^LOGL}^{n1}, n1 = tid mod LP
+template <int R0, int LOGS, int I>
+__device__ inline void blue_roots(const double2* __restrict__ ws, double2* wp, int tid)
+{
+  constexpr int LOGL = LOGS - 3 * I, LP = 1 << (LOGL - FftShape<LOGS>::lr(I));
+  if constexpr (LP > 1) {
+    static_assert(BlueShape<R0, LOGS>::threads % LP == 0, "one root per thread");
+    wp[I] = ws[(tid & (LP - 1)) << (LOGS - LOGL)];
+    blue_roots<R0, LOGS, I + 1>(ws, wp, tid);
+  }
 }
 
 struct BlueTables {
@@ -866,7 +900,9 @@ struct BlueTables {
 
 // One workgroup per segment; the PSD is the given white level (no estimate).
 template <int R0, int LOGS>
-__global__ __launch_bounds__((BlueShape<R0, LOGS>::threads)) void strain_blue_kernel(
+// (S = 64 held to 128 registers, four wavefronts per SIMD: 20 k segments of 602 samples 109 -> 94 us)
+__global__ __launch_bounds__((BlueShape<R0, LOGS>::threads))
+__attribute__((amdgpu_waves_per_eu(LOGS == 6 ? 4 : 1))) void strain_blue_kernel(
     const double* __restrict__ x, int64_t n_total, int32_t n_seg, int32_t M, double dt, double s_white, int32_t k_lo,
     int32_t n_bins, BlueTables tt, double* __restrict__ bins, double* __restrict__ psd, int32_t* __restrict__ keep)
 {
@@ -881,6 +917,10 @@ __global__ __launch_bounds__((BlueShape<R0, LOGS>::threads)) void strain_blue_ke
   if (tid == 0) s_bad = 0;
   __syncthreads();
   bool bad = false;
+  // the roots of the passes' twiddles
+  double2 wp[FftShape<LOGS>::NP], h[8], w0 = make_double2(1.0, 0.0);
+  blue_roots<R0, LOGS, 0>(tt.ws, wp, tid);
+  if (tid < S) w0 = tt.wl[tid];
   if (tid < S) {
     // z[j] conj(b[j]), zero from M on, through the radix-R0 pass
     const bool al = (reinterpret_cast<uintptr_t>(xs) & 15) == 0;
@@ -897,16 +937,19 @@ __global__ __launch_bounds__((BlueShape<R0, LOGS>::threads)) void strain_blue_ke
       }
     }
     dft_any<R0>(v);
+    double2 wv[R0];
+    powers<R0>(w0, wv);
 #pragma unroll
-    for (int k = 0; k < R0; ++k) buf[swz(tid + S * k)] = k == 0 ? v[0] : cmul(v[k], tt.wl[tid * k]);
+    for (int k = 0; k < R0; ++k) buf[swz(tid + S * k)] = k == 0 ? v[0] : cmul(v[k], wv[k]);
   }
   if (bad) s_bad = 1;
   __syncthreads();
-  blue_pass<R0, LOGS, 0, false>(buf, tt.ws, tt.bh, tid);
+  blue_pass<R0, LOGS, 0, false>(buf, wp, tt.bh, h, tid);
   if (tid < S) {
-    double2 v[R0];
+    double2 v[R0], wv[R0];
+    powers<R0>(w0, wv);
 #pragma unroll
-    for (int k = 0; k < R0; ++k) v[k] = k == 0 ? buf[swz(tid)] : cmul(buf[swz(tid + S * k)], tt.wl[tid * k]);
+    for (int k = 0; k < R0; ++k) v[k] = k == 0 ? buf[swz(tid)] : cmul(buf[swz(tid + S * k)], wv[k]);
     dft_any<R0>(v);
     // Z[j] = conj(b[j]) conj(v): each thread's points are its own, no barrier in between
 #pragma unroll
