@@ -1263,13 +1263,16 @@ __global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
     cs.kappa = cn.kappa - ddphi * T / (2.0 * kPi);   // dphi/dt = -dphi/dtau
     cs.phase = cn.phase + dphi;
     cs.amp = cn.amp * exp(sa.c_amp * y2);
-    cs.beta = cn.beta * pow(cs.kappa / cn.kappa, 11.0 / 3.0);
+    const double kr = cs.kappa / cn.kappa, kr2 = kr * kr;
+    cs.beta = cn.beta * kr2 * kr2 * inv_root3(kr);   // beta ~ kappa^(11/3)
     cs.dres = (11.0 / 24.0) * cs.beta * cs.beta / cs.kappa;
     if (valid) store(g, cs);
     // judge term: A_PN^2 T / S_r(f_PN) exp(i dphi) sinc(dkappa), summed over the group's rows
     const Chirp cp = pn35_chirp(tau, pm.nu, pm.inv5Mnu, pm.Mt, pm.nu25, phic, T, pc);
     const double dk = cs.kappa - cp.kappa;
-    const double snc = fabs(dk) < 1e-8 ? 1.0 - kPi * kPi * dk * dk / 6.0 : sin(kPi * dk) / (kPi * dk);
+    double sk, ck;
+    sincos64(kPi * dk, sk, ck);
+    const double snc = fabs(dk) < 1e-8 ? 1.0 - kPi * kPi * dk * dk / 6.0 : sk / (kPi * dk);
     double inv_s = 0.0;
     for (int d = 0; d < SFT_GROUP_MAX; ++d) {
       const int rr = g_rows[g * SFT_GROUP_MAX + d];
@@ -1279,7 +1282,7 @@ __global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
     }
     const double wt = cp.amp * cp.amp * T * inv_s;
     double sd, cd;
-    sincos(cs.phase - cp.phase, &sd, &cd);
+    sincos64(cs.phase - cp.phase, sd, cd);
     sr += wt * cd * snc;
     si += wt * sd * snc;
     sw += wt;

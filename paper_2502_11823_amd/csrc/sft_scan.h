@@ -455,41 +455,69 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
     if constexpr (KERN == KERN_FRESNEL) dir = fabs(ch.beta) <= a.beta_switch;
     if (dir) {
       // H_j = sin(pi delta) / (pi (delta - j))
-      const R dl = (R)delta;
-      R sp;
       if constexpr (PREC == SFT_PREC_FP64) {
-        sp = sin(kPi * delta) / kPi;
+        // bins j and -j in pairs from the edges inwards, one reciprocal each: with u = 1 / (delta^2 - j^2),
+        // H_j = sp (delta + j) u and H_-j = sp (delta - j) u; |delta| <= 1/2 keeps them apart from j = 0,
+        // whose weight is sinc(delta)
+        const double w0 = sinc64(delta * delta), sp = delta * w0;
+        auto drun = [&](auto stgc) {
+          constexpr bool STG = decltype(stgc)::value;
+          auto mac = [&](int j, double h) {
+            const int idx = i0 + j + K;
+            if (!STG && !inband && (idx < 0 || idx >= a.n_ext)) {
+              fl |= kFlagOOB;
+              return;
+            }
+#pragma unroll
+            for (int d = 0; d < ND; ++d) {
+              R bre, bim;
+              if constexpr (STG) BinIO<Bin>::load(sw + d * WST + (idx - sb), bre, bim);
+              else BinIO<Bin>::load(rp[d] + idx, bre, bim);
+              cre[d] = fma(bre, h, cre[d]);
+              cim[d] = fma(bim, h, cim[d]);
+            }
+          };
+#pragma unroll SFT_BIN_UNROLL
+          for (int j = K; j >= 1; --j) {
+            const double xm = delta - (double)j, xp = delta + (double)j;
+            const double u = sp * rcp64(xm * xp);
+            mac(-j, xm * u);
+            mac(j, xp * u);
+          }
+          mac(0, w0);
+        };
+        if (stg) drun(std::true_type{});
+        else drun(std::false_type{});
       } else {
+        const R dl = (R)delta;
         float s_, c_;
         phasor(kPi * delta, s_, c_);
-        sp = s_ * kInvPiF;
-      }
-      auto drun = [&](auto stgc) {
-        constexpr bool STG = decltype(stgc)::value;
+        const float sp = s_ * kInvPiF;
+        auto drun = [&](auto stgc) {
+          constexpr bool STG = decltype(stgc)::value;
 #pragma unroll SFT_BIN_UNROLL
-        for (int t = 0; t <= 2 * K; ++t) {
-          const int j = bin_order(t, K);
-          const int idx = i0 + j + K;
-          if (!STG && !inband && (idx < 0 || idx >= a.n_ext)) {
-            fl |= kFlagOOB;
-            continue;
-          }
-          const R x = dl - (R)j;
-          R h;
-          if constexpr (PREC == SFT_PREC_FP64) h = (x == (R)0) ? (R)1 : sp / x;
-          else h = (x == (R)0) ? (R)1 : (R)(sp * fast_rcp((float)x));
+          for (int t = 0; t <= 2 * K; ++t) {
+            const int j = bin_order(t, K);
+            const int idx = i0 + j + K;
+            if (!STG && !inband && (idx < 0 || idx >= a.n_ext)) {
+              fl |= kFlagOOB;
+              continue;
+            }
+            const R x = dl - (R)j;
+            const R h = (x == (R)0) ? (R)1 : (R)(sp * fast_rcp((float)x));
 #pragma unroll
-          for (int d = 0; d < ND; ++d) {
-            R bre, bim;
-            if constexpr (STG) BinIO<Bin>::load(sw + d * WST + (idx - sb), bre, bim);
-            else BinIO<Bin>::load(rp[d] + idx, bre, bim);
-            cre[d] = fma(bre, h, cre[d]);
-            cim[d] = fma(bim, h, cim[d]);
+            for (int d = 0; d < ND; ++d) {
+              R bre, bim;
+              if constexpr (STG) BinIO<Bin>::load(sw + d * WST + (idx - sb), bre, bim);
+              else BinIO<Bin>::load(rp[d] + idx, bre, bim);
+              cre[d] = fma(bre, h, cre[d]);
+              cim[d] = fma(bim, h, cim[d]);
+            }
           }
-        }
-      };
-      if (stg) drun(std::true_type{});
-      else drun(std::false_type{});
+        };
+        if (stg) drun(std::true_type{});
+        else drun(std::false_type{});
+      }
     } else if constexpr (KERN == KERN_FRESNEL && PREC == SFT_PREC_FP64) {
       // FP64 Fresnel weights, bin by bin.  With b = |beta|, the mirror x' = ds - jj (ds = +-delta,
       // jj = +-j, the lower signs for beta < 0, where F(x, beta) = conj F(-x, b)) and
@@ -779,9 +807,8 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
     // term_d = (-1)^{k0} A exp(i phi) C_d
     R pc, ps;
     if constexpr (PREC == SFT_PREC_FP64) {
-      const double ph = reduce_2pi(ch.phase);
       double s_, c_;
-      sincos(ph, &s_, &c_);
+      sincos64(ch.phase, s_, c_);
       ps = (R)s_;
       pc = (R)c_;
     } else {
