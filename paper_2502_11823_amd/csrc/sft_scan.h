@@ -166,7 +166,8 @@ constexpr uint32_t kOneEntered = 1u << 31;   // the group entered the sums
 // Register budget: the FP32 Fresnel kernels with a compile-time window for groups of 2 or 3
 // rows, and the one-row K = 32 kernel, with the Newtonian chirp fit 96 VGPRs without
 // spilling, i.e. 5 wavefronts per SIMD instead of 4; the FP32 Dirichlet kernels with the
-// 3.5PN chirp fit 168, i.e. 3 instead of 2.  The others are left to the compiler (1 = no
+// 3.5PN chirp fit 168, i.e. 3 instead of 2; the FP64 Fresnel kernels with it are held to 256, i.e. 2
+// instead of 1 (2000 templates x 300 SFT triples 1060 us at 1).  The others are left to the compiler (1 = no
 // constraint).
 template <int PREC, int KERN, int KC, int ND, int WF>
 constexpr int scan_min_waves()
@@ -175,6 +176,7 @@ constexpr int scan_min_waves()
       (ND == 2 || ND == 3 || (ND == 1 && KC == 32)))
     return 5;
   if (PREC != SFT_PREC_FP64 && KERN == KERN_DIRICHLET && WF == WF_PN35) return 3;
+  if (PREC == SFT_PREC_FP64 && KERN == KERN_FRESNEL && WF == WF_PN35) return 2;
   return 1;
 }
 
