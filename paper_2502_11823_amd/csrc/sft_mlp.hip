@@ -761,7 +761,7 @@ static hipError_t mlp_bf16_launch(const sft_surrogate* s, const double* U, int64
 // ---------------------------------------------------------------------------- inference
 size_t mlp_infer_scratch_bytes(int hidden, int64_t chunk)
 {
-  if (mlp_fused_ok(hidden)) return 256;
+  if (mlp_fused_ok(hidden)) return 0;   // every BF16 width is among these
   return 2 * (size_t)(2 * chunk) * (size_t)std::max(hidden, 3) * sizeof(double) + 256;
 }
 
@@ -1613,11 +1613,13 @@ extern "C" sft_status sft_surrogate_infer(const sft_surrogate* s, const double* 
   if (!u || !y || !dy) return mlp_fail(SFT_E_INVALID, "sft_surrogate_infer: null argument");
   hipStream_t st = (hipStream_t)hip_stream;
   const int64_t chunk = std::min<int64_t>(n, 1 << 16);
+  // the fused kernels need no scratch: the pair of stream-ordered calls took 15 of 26 us for 1000 rows
+  const size_t bytes = mlp_infer_scratch_bytes(s->d.hidden, chunk);
   void* ws = nullptr;
-  hipError_t e = hipMallocAsync(&ws, mlp_infer_scratch_bytes(s->d.hidden, chunk), st);
+  hipError_t e = bytes ? hipMallocAsync(&ws, bytes, st) : hipSuccess;
   if (e != hipSuccess) return mlp_fail(SFT_E_NOMEM, "sft_surrogate_infer", e);
   e = mlp_infer(s, u, n, y, dy, ws, chunk, st);
-  hipError_t e2 = hipFreeAsync(ws, st);
+  hipError_t e2 = bytes ? hipFreeAsync(ws, st) : hipSuccess;
   if (e != hipSuccess) return mlp_fail(SFT_E_DEVICE, "sft_surrogate_infer", e);
   if (e2 != hipSuccess) return mlp_fail(SFT_E_DEVICE, "sft_surrogate_infer: free", e2);
   return SFT_OK;
