@@ -90,8 +90,8 @@ template <> struct BinIO<bf16x2> {
 
 // ---------------------------------------------------------------- FP64 functions
 // The FP64 paths are bound by FP64 instructions, most of them special functions; the ones below are for
-// the ranges that occur and cost a third of the library's (no large-argument, subnormal or exact-rounding
-// branches), within two ulp.  30 k 3.5PN templates x 256 SFTs in FP64: 243 us with the library's, 195 us so.
+// the ranges that occur and leave out what the library has to have (large arguments, subnormals, exact rounding:
+// no branches), within two ulp.  30 k 3.5PN templates x 256 SFTs in FP64: 243 us with the library's, 195 us so.
 
 // 1 / x and 1 / sqrt(x), x normal: the hardware estimate and two Newton steps
 __device__ inline double rcp64(double x)
