@@ -149,7 +149,11 @@ __device__ inline double sinc64(double z)
   return p;
 }
 
-// n = phi / (pi / 2) rounded to the nearest integer (|n| < 2^51) and its low 32 bits: adding 1.5 * 2^52
+// Phases that quarter_turns holds for, with everything that takes its remainder r: beyond, r leaves
+// [-pi/4, pi/4], and the series in r are not bounded
+constexpr double kPhaseMax = 1125899906842624.0;   // 2^50
+
+// n = phi / (pi / 2) rounded to the nearest integer and its low 32 bits (|phi| < kPhaseMax): adding 1.5 * 2^52
 // leaves the integer in the low bits of the sum
 __device__ inline double quarter_turns(double phi, int& q)
 {
@@ -159,8 +163,8 @@ __device__ inline double quarter_turns(double phi, int& q)
   return t - magic;
 }
 
-// (sin phi, cos phi) of an unreduced phase: phi = n pi/2 + r, |r| <= pi/4, by a two-constant Cody-Waite
-// reduction, the Maclaurin series to r^15 and r^16, and the quadrant by swapping and negating
+// (sin phi, cos phi) of an unreduced phase, |phi| < kPhaseMax: phi = n pi/2 + r, |r| <= pi/4, by a two-constant
+// Cody-Waite reduction, the Maclaurin series to r^15 and r^16, and the quadrant by swapping and negating
 __device__ inline void sincos64(double phi, double& s, double& c)
 {
   int q;

@@ -1270,8 +1270,14 @@ __global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
     // judge term: A_PN^2 T / S_r(f_PN) exp(i dphi) sinc(dkappa), summed over the group's rows
     const Chirp cp = pn35_chirp(tau, pm.nu, pm.inv5Mnu, pm.Mt, pm.nu25, phic, T, pc);
     const double dk = cs.kappa - cp.kappa;
+    // a diverged network's phases have any size, and the judge is there for it: the library's sine past kPhaseMax
+    // keeps every term within its weight
+    auto phase_sincos = [](double p, double& s, double& c) {
+      if (fabs(p) < kPhaseMax) sincos64(p, s, c);
+      else sincos(p, &s, &c);
+    };
     double sk, ck;
-    sincos64(kPi * dk, sk, ck);
+    phase_sincos(kPi * dk, sk, ck);
     const double snc = fabs(dk) < 1e-8 ? 1.0 - kPi * kPi * dk * dk / 6.0 : sk / (kPi * dk);
     double inv_s = 0.0;
     for (int d = 0; d < SFT_GROUP_MAX; ++d) {
@@ -1282,7 +1288,7 @@ __global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
     }
     const double wt = cp.amp * cp.amp * T * inv_s;
     double sd, cd;
-    sincos64(cs.phase - cp.phase, sd, cd);
+    phase_sincos(cs.phase - cp.phase, sd, cd);
     sr += wt * cd * snc;
     si += wt * sd * snc;
     sw += wt;
