@@ -334,17 +334,20 @@ __device__ inline double reduce_2pi(double phi)
   return fma(-n, kTwoPiLo, r);
 }
 
+constexpr double kTwoOverPi = 0.63661977236758134308;
 constexpr double kPiO2Hi = 1.5707963267948966192;     // nearest double to pi/2
 constexpr double kPiO2Lo = 6.123233995736766036e-17;  // pi/2 - kPiO2Hi
 
 // (sin phi, cos phi) in FP32 for an unreduced FP64 phase: phi = n pi/2 + r with
-// |r| <= pi/4 by a two-constant Cody-Waite reduction in FP64, then the Maclaurin
+// |r| <= pi/4 by a two-constant Cody-Waite reduction in FP64 (|n| < 2^53), then the Maclaurin
 // series of sin and cos on [-pi/4, pi/4] in FP32 (truncation < 1e-11), and the
-// quadrant n mod 4 applied by swapping and negating.
+// quadrant n mod 4 applied by swapping and negating.  n and its quadrant by rint and a conversion:
+// quarter_turns holds for a quarter of these phases only, and with it the kernels of the widest groups
+// need two registers more, which costs them a wavefront per SIMD (start reference, three rows, K = 13:
+// 1060 us so, 1205 us with it).
 __device__ inline void phasor(double phi, float& s, float& c)
 {
-  int q;
-  const double n = quarter_turns(phi, q);
+  const double n = rint(phi * kTwoOverPi);
   double r = fma(-n, kPiO2Hi, phi);
   r = fma(-n, kPiO2Lo, r);
   const float x = (float)r;
@@ -353,6 +356,7 @@ __device__ inline void phasor(double phi, float& s, float& c)
                                                           -1.98412698e-4f), 8.33333333e-3f), -1.66666667e-1f), 1.0f);
   const float cp = fmaf(x2, fmaf(x2, fmaf(x2, fmaf(x2, fmaf(x2, fmaf(x2, 2.08767570e-9f, -2.75573192e-7f),
                                                               2.48015873e-5f), -1.38888889e-3f), 4.16666667e-2f), -0.5f), 1.0f);
+  const int q = (int)((long long)n & 3);
   const float s0 = (q & 1) ? cp : sp;
   const float c0 = (q & 1) ? sp : cp;
   s = (q & 2) ? -s0 : s0;

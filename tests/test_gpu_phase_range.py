@@ -1,0 +1,28 @@
+"""Phases of any size: a phi_c that is no angle (2^51 quarter turns and beyond) still gives terms of modulus one,
+with the sine and cosine of the phase as FP64 holds it."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2502_11823_amd import sft, synth
+from parity_helpers import compare, gpu_scan, orc_scan
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(phi_c, **kw):
+    w = synth.tiny(seed=3, n_templates=1, n_sft=20, noise_series=False)
+    bank = synth.uniform_bank(40, 1.19, 1.21, 20 * 64.0 + 600.0, 9, q_lo=1.0, q_hi=2.0, n_sft=w.n_sft)
+    bank["phi_c"] = np.full(40, phi_c)
+    g = gpu_scan(sft.SFTData.from_workload(w, storage="f64" if kw["precision"] == "fp64" else "f32"), bank, **kw)
+    return g, orc_scan(w, bank, **kw)
+
+
+@pytest.mark.parametrize("kernel,K", [("dirichlet", 4), ("dirichlet", 8), ("auto", 8), ("auto", 13)])
+@pytest.mark.parametrize("waveform", ["newton", "pn35"])
+@pytest.mark.parametrize("phi_c", [1e15, 4e15, -4e15, 6.1e15, -8.7e15])
+def test_fp32_sums(phi_c, waveform, kernel, K):
+    # FP64 phases and FP32 sums: the bounds of the ordinary phases
+    g, o = _case(phi_c, K=K, kernel=kernel, precision="fp32_kahan", waveform=waveform)
+    compare(g, o, label="phi_c %g %s %s" % (phi_c, waveform, kernel))
