@@ -334,6 +334,14 @@ __device__ inline double reduce_2pi(double phi)
   return fma(-n, kTwoPiLo, r);
 }
 
+// A phase of any size for sincos64: phi itself, or from kPhaseMax on its remainder.  Each reduction leaves less than
+// 2^-50 of the phase, so that the largest take 20 of them.
+__device__ inline double bounded_phase(double phi)
+{
+  for (int i = 0; i < 24 && fabs(phi) >= kPhaseMax; ++i) phi = reduce_2pi(phi);
+  return phi;
+}
+
 constexpr double kTwoOverPi = 0.63661977236758134308;
 constexpr double kPiO2Hi = 1.5707963267948966192;     // nearest double to pi/2
 constexpr double kPiO2Lo = 6.123233995736766036e-17;  // pi/2 - kPiO2Hi

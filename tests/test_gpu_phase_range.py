@@ -26,3 +26,22 @@ def test_fp32_sums(phi_c, waveform, kernel, K):
     # FP64 phases and FP32 sums: the bounds of the ordinary phases
     g, o = _case(phi_c, K=K, kernel=kernel, precision="fp32_kahan", waveform=waveform)
     compare(g, o, label="phi_c %g %s %s" % (phi_c, waveform, kernel))
+
+
+@pytest.mark.parametrize("kernel,K", [("dirichlet", 4), ("dirichlet", 9)])
+@pytest.mark.parametrize("waveform", ["newton", "pn35"])
+@pytest.mark.parametrize("phi_c", [1e15, 1.2e15, -4e15, 6.1e15, 1.3e18, -1.3e18, 7e21])
+def test_fp64_sums(phi_c, waveform, kernel, K):
+    # the bounds of the ordinary phases; the reduction's second constant of 2 pi is good to 1e-32 a turn
+    g, o = _case(phi_c, K=K, kernel=kernel, precision="fp64", waveform=waveform)
+    compare(g, o, label="phi_c %g %s %s" % (phi_c, waveform, kernel), tol_z=1e-9, tol_rho=1e-9, tol_hh=1e-9)
+
+
+@pytest.mark.parametrize("phi_c", [1e35, -1e120, 1.7e308])
+def test_fp64_terms_stay_bounded(phi_c):
+    # no digit of such a phase is left, but every term keeps its modulus: z of noise alone stays near sqrt(<h, h>)
+    kw = dict(K=4, kernel="dirichlet", precision="fp64")
+    g, _ = _case(phi_c, **kw)
+    z, _ = _case(0.0, **kw)
+    assert np.all(np.isfinite(g["zp"])) and np.all(np.abs(g["zp"]) <= 10 * np.sqrt(g["hhp"]))
+    assert np.allclose(g["hhp"], z["hhp"], rtol=1e-12, atol=0)
