@@ -166,8 +166,7 @@ constexpr uint32_t kOneEntered = 1u << 31;   // the group entered the sums
 // Register budget: the FP32 Fresnel kernels with a compile-time window for groups of 2 or 3
 // rows, and the one-row K = 32 kernel, with the Newtonian chirp fit 96 VGPRs without
 // spilling, i.e. 5 wavefronts per SIMD instead of 4; the FP32 Dirichlet kernels with the
-// 3.5PN chirp fit 168, i.e. 3 instead of 2; the FP64 Fresnel kernels with it are held to 256, i.e. 2
-// instead of 1 (2000 templates x 300 SFT triples 1060 us at 1).  The others are left to the compiler (1 = no
+// 3.5PN chirp fit 168, i.e. 3 instead of 2.  The others are left to the compiler (1 = no
 // constraint).
 template <int PREC, int KERN, int KC, int ND, int WF>
 constexpr int scan_min_waves()
@@ -176,7 +175,6 @@ constexpr int scan_min_waves()
       (ND == 2 || ND == 3 || (ND == 1 && KC == 32)))
     return 5;
   if (PREC != SFT_PREC_FP64 && KERN == KERN_DIRICHLET && WF == WF_PN35) return 3;
-  if (PREC == SFT_PREC_FP64 && KERN == KERN_FRESNEL && WF == WF_PN35) return 2;
   return 1;
 }
 
@@ -286,6 +284,11 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
   using R = typename PrecTraits<PREC>::R;
   using Acc = typename std::conditional<ONE != 0, AccTerm<R>, typename PrecTraits<PREC>::Acc>::type;
   using PS = typename std::conditional<PREC == SFT_PREC_FP64, double, float>::type;
+  // The FP64 Dirichlet kernels take their own sine and cosine and the bins in pairs.  The FP64 Fresnel kernels keep the
+  // library's and the bins one by one (for the drifts below beta_switch): their time goes into the Fresnel weights, and
+  // the registers of the other form cost them a wavefront per SIMD (100 k Newtonian templates x 60 groups 2.98 ms so,
+  // 3.50 ms with it) and the 3.5PN ones up to 92 bytes of scratch.
+  constexpr bool kOwn64 = PREC == SFT_PREC_FP64 && KERN == KERN_DIRICHLET;
   const int g0 = ONE ? c : c * a.chunk;
   const int g1 = ONE ? c : min(g0 + a.chunk, a.n_groups) - 1;
   const int lo = a.a_first ? (int)a.a_first[m] : 0;
@@ -417,9 +420,9 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
     // templates 199 us, 202 us with a branch for the phase, 195 us without a bound).  Frequencies below 0 are
     // refused further down.
     double far = ch.kappa;
-    if constexpr (PREC == SFT_PREC_FP64) far = fma(fabs(ch.phase), 1.0e9 / kPhaseMax, far);
+    if constexpr (kOwn64) far = fma(fabs(ch.phase), 1.0e9 / kPhaseMax, far);
     if (!(far < 1.0e9)) {
-      if (!(ch.kappa < 1.0e9)) {
+      if (!kOwn64 || !(ch.kappa < 1.0e9)) {
         // no window bin and no norm bin exists
         fl |= kFlagOOB;
         continue;
@@ -465,7 +468,7 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
     if constexpr (KERN == KERN_FRESNEL) dir = fabs(ch.beta) <= a.beta_switch;
     if (dir) {
       // H_j = sin(pi delta) / (pi (delta - j))
-      if constexpr (PREC == SFT_PREC_FP64) {
+      if constexpr (kOwn64) {
         // bins j and -j in pairs from the edges inwards, one reciprocal each: with u = 1 / (delta^2 - j^2),
         // H_j = sp (delta + j) u and H_-j = sp (delta - j) u; |delta| <= 1/2 keeps them apart from j = 0,
         // whose weight is sinc(delta)
@@ -500,9 +503,14 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
         else drun(std::false_type{});
       } else {
         const R dl = (R)delta;
-        float s_, c_;
-        phasor(kPi * delta, s_, c_);
-        const float sp = s_ * kInvPiF;
+        R sp;
+        if constexpr (PREC == SFT_PREC_FP64) {
+          sp = sin(kPi * delta) / kPi;
+        } else {
+          float s_, c_;
+          phasor(kPi * delta, s_, c_);
+          sp = s_ * kInvPiF;
+        }
         auto drun = [&](auto stgc) {
           constexpr bool STG = decltype(stgc)::value;
 #pragma unroll SFT_BIN_UNROLL
@@ -514,7 +522,9 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
               continue;
             }
             const R x = dl - (R)j;
-            const R h = (x == (R)0) ? (R)1 : (R)(sp * fast_rcp((float)x));
+            R h;
+            if constexpr (PREC == SFT_PREC_FP64) h = (x == (R)0) ? (R)1 : sp / x;
+            else h = (x == (R)0) ? (R)1 : (R)(sp * fast_rcp((float)x));
 #pragma unroll
             for (int d = 0; d < ND; ++d) {
               R bre, bim;
@@ -816,11 +826,10 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
     }
     // term_d = (-1)^{k0} A exp(i phi) C_d
     R pc, ps;
-    if constexpr (PREC == SFT_PREC_FP64) {
-      double s_, c_;
-      sincos64(ch.phase, s_, c_);
-      ps = (R)s_;
-      pc = (R)c_;
+    if constexpr (kOwn64) {
+      sincos64(ch.phase, ps, pc);
+    } else if constexpr (PREC == SFT_PREC_FP64) {
+      sincos(reduce_2pi(ch.phase), &ps, &pc);
     } else {
       float s_, c_;
       phasor(ch.phase, s_, c_);

@@ -28,7 +28,7 @@ def test_fp32_sums(phi_c, waveform, kernel, K):
     compare(g, o, label="phi_c %g %s %s" % (phi_c, waveform, kernel))
 
 
-@pytest.mark.parametrize("kernel,K", [("dirichlet", 4), ("dirichlet", 9)])
+@pytest.mark.parametrize("kernel,K", [("dirichlet", 4), ("dirichlet", 9), ("auto", 4), ("auto", 9)])
 @pytest.mark.parametrize("waveform", ["newton", "pn35"])
 @pytest.mark.parametrize("phi_c", [1e15, 1.2e15, -4e15, 6.1e15, 1.3e18, -1.3e18, 7e21])
 def test_fp64_sums(phi_c, waveform, kernel, K):
@@ -37,10 +37,11 @@ def test_fp64_sums(phi_c, waveform, kernel, K):
     compare(g, o, label="phi_c %g %s %s" % (phi_c, waveform, kernel), tol_z=1e-9, tol_rho=1e-9, tol_hh=1e-9)
 
 
+@pytest.mark.parametrize("kernel", ["dirichlet", "auto"])
 @pytest.mark.parametrize("phi_c", [1e35, -1e120, 1.7e308])
-def test_fp64_terms_stay_bounded(phi_c):
+def test_fp64_terms_stay_bounded(phi_c, kernel):
     # no digit of such a phase is left, but every term keeps its modulus: z of noise alone stays near sqrt(<h, h>)
-    kw = dict(K=4, kernel="dirichlet", precision="fp64")
+    kw = dict(K=4, kernel=kernel, precision="fp64")
     g, _ = _case(phi_c, **kw)
     z, _ = _case(0.0, **kw)
     assert np.all(np.isfinite(g["zp"])) and np.all(np.abs(g["zp"]) <= 10 * np.sqrt(g["hhp"]))
