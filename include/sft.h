@@ -354,10 +354,11 @@ enum { SFT_ORDER_GIVEN = 0, SFT_ORDER_TRACK = 1 };
  * chunk_groups: timestamp groups (SFT rows sharing a start time, one per detector) per
  * work item; a work item is (template tile, chunk), and partial sums are combined in a
  * fixed order (default: chunks of about 1 MiB of bins and at least four work items per
- * resident workgroup, or with FP64 sums chunks that grow with the square root of the groups
- * per resident workgroup).  persistent: 1 launches one workgroup per
+ * resident workgroup, or with FP64 Dirichlet sums chunks that grow with the square root of
+ * the groups per resident workgroup).  persistent: 1 launches one workgroup per
  * resident slot, each pulling work items from a device counter until the queue is empty; 0
- * launches one workgroup per item.
+ * launches one workgroup per item.  An all-zero tuning selects the automatic chunks with one
+ * workgroup per item, and with FP64 Fresnel weights the persistent grid.
  * order: SFT_ORDER_GIVEN scans the bank in the caller's order, which is fast when
  * neighbouring templates have nearly equal frequency tracks (a bank sorted by chirp mass at
  * one coalescence time, say).  SFT_ORDER_TRACK first sorts the bank on the device by (first

@@ -843,6 +843,15 @@ static void layout_ws(Prepared& P)
   P.ws_bytes = P.counter_off + 256;
 }
 
+// The grid of the automatic launch shape: plain, as the items come in the same order without the counter (1000
+// templates on three detectors 163 us against 172 us, 200 k space-like 453 and 453 us), but persistent with the FP64
+// Fresnel weights, whose long items a plain grid hands out worse (100 k Newtonian templates x 60 groups 3.10 ms
+// against 2.97 ms, 10 k 3.5PN ones 0.58 ms against 0.50 ms).
+static int auto_persistent(const sft_opts* o)
+{
+  return o->precision == SFT_PREC_FP64 && o->kernel != SFT_KERNEL_DIRICHLET;
+}
+
 static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t n, const sft_opts* o,
                                const sft_tuning& t, Prepared& P, bool fs, int wf = -1, const double* wtab = nullptr,
                                const uint32_t* xflags = nullptr)
@@ -892,15 +901,17 @@ static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t 
   } else {
     // automatic: chunks of at most about 1 MiB of bins (they stay in L2 while the tiles of the chunk run).
     // FP32 sums: at least ~4 work items per resident workgroup (short last wave); where a chunk ends enters
-    // these sums at 2e-8 of the result, so their chunks are kept.  FP64 sums: c = sqrt(1.5 N) groups, N the
-    // groups that a resident workgroup works through in all, as a work item costs about 1.5 groups beside
+    // these sums at 2e-8 of the result, so their chunks are kept.  FP64 Dirichlet sums: c = sqrt(1.5 N) groups,
+    // N the groups that a resident workgroup works through in all, as a work item costs about 1.5 groups beside
     // its own (its prologue and its partial sums) and the last items leave the chip idle for about c (30 k
-    // 3.5PN templates x 256 groups: 255 us with 4 items per resident workgroup, 242 us so).
+    // 3.5PN templates x 256 groups: 255 us with 4 items per resident workgroup, 242 us so).  The groups of the
+    // FP64 Fresnel weights cost many times more, and their chunks are those of the FP32 sums (100 k Newtonian
+    // templates x 60 groups 2.98 ms, 3.14 ms by the square root).
     const size_t bin_sz = d->storage == SFT_STORE_F64 ? 16 : d->storage == SFT_STORE_F32 ? 8 : 4;
     const size_t group_bytes = (size_t)d->nd * d->n_ext * bin_sz;
     const int64_t g_l2 = std::max<int64_t>(1, (int64_t)((1u << 20) / std::max<size_t>(group_bytes, 1)));
     int64_t nc_work = (4 * resident + a.n_tiles - 1) / a.n_tiles;
-    if (o->precision == SFT_PREC_FP64) {
+    if (o->precision == SFT_PREC_FP64 && o->kernel == SFT_KERNEL_DIRICHLET) {
       const double N = (double)d->n_groups * a.n_tiles / (double)resident;
       const int64_t c = std::max<int64_t>(4, (int64_t)std::sqrt(1.5 * N));
       nc_work = (d->n_groups + c - 1) / c;
@@ -913,9 +924,8 @@ static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t 
   a.n_chunks = (d->n_groups + a.chunk - 1) / a.chunk;
   if ((int64_t)a.n_tiles * a.n_chunks > INT32_MAX) return fail(SFT_E_RANGE, "scan: too many work items");
   a.n_items = a.n_tiles * a.n_chunks;
-  // a plain grid unless asked for: the items come in the same order, without the counter (1000 templates on
-  // three detectors 163 us against 172 us, 200 k space-like 453 and 453 us)
-  a.persistent = t.persistent;
+  const bool automatic = t.block == 0 && t.chunk_groups == 0 && t.persistent == 0;
+  a.persistent = automatic ? auto_persistent(o) : t.persistent;
   P.block = dim3(B);
   if (a.persistent) P.grid = dim3((unsigned)std::min<int64_t>(a.n_items, resident));
   else P.grid = dim3((unsigned)a.n_tiles, (unsigned)a.n_chunks);
@@ -1513,6 +1523,7 @@ extern "C" sft_status sft_template_bank_scan_noalloc(const sft_data* d, const sf
     if (nc_max < 1)
       return fail(SFT_E_RANGE, "scan (no-alloc): %lld templates need %zu bytes of partial sums, more than the %u-byte scratch",
                   (long long)n, per_chunk, (unsigned)SFT_NOALLOC_SCRATCH_BYTES);
+    if (t.block == 0 && t.chunk_groups == 0 && t.persistent == 0) t.persistent = auto_persistent(o);   // the automatic grid
     t.chunk_groups = (int32_t)((d->n_groups + nc_max - 1) / nc_max);
     if ((s = prepare_scan(d, bank, n, o, t, P, fs)) != SFT_OK) return s;
     if (P.ws_bytes > SFT_NOALLOC_SCRATCH_BYTES)
