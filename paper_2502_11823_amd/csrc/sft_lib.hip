@@ -640,22 +640,24 @@ __global__ __launch_bounds__(kFinBlock) void finalize_kernel(
       used += pf >> kUsedShift;
     }
   }
-  // the slices of each template, slice h + i into slice i
-  __shared__ double sv[7][kFinBlock];
-  __shared__ uint32_t sf[kFinBlock], su[kFinBlock];
+  if constexpr (S > 1) {
+    // the slices of each template, slice h + i into slice i
+    __shared__ double sv[7][kFinBlock];
+    __shared__ uint32_t sf[kFinBlock], su[kFinBlock];
 #pragma unroll
-  for (int q = 0; q < 7; ++q) sv[q][threadIdx.x] = v[q];
-  sf[threadIdx.x] = fl;
-  su[threadIdx.x] = used;
+    for (int q = 0; q < 7; ++q) sv[q][threadIdx.x] = v[q];
+    sf[threadIdx.x] = fl;
+    su[threadIdx.x] = used;
 #pragma unroll
-  for (int h = S / 2; h > 0; h >>= 1) {
-    __syncthreads();
-    if (s < h) {
-      const int o = (int)threadIdx.x + h * T;
+    for (int h = S / 2; h > 0; h >>= 1) {
+      __syncthreads();
+      if (s < h) {
+        const int o = (int)threadIdx.x + h * T;
 #pragma unroll
-      for (int q = 0; q < 7; ++q) sv[q][threadIdx.x] = v[q] += sv[q][o];
-      sf[threadIdx.x] = fl |= sf[o];
-      su[threadIdx.x] = used += su[o];
+        for (int q = 0; q < 7; ++q) sv[q][threadIdx.x] = v[q] += sv[q][o];
+        sf[threadIdx.x] = fl |= sf[o];
+        su[threadIdx.x] = used += su[o];
+      }
     }
   }
   if (s != 0 || m >= n) return;
@@ -965,9 +967,14 @@ static hipError_t enqueue_scan(Prepared& P, void* ws, sft_out* out, hipStream_t 
   // One template: its chunks over the whole workgroup.  A bank whose workgroups of 64 templates
   // fill the chip by themselves (1024 of them, four per CU) keeps whole 512-byte rows: 1e5
   // templates x 46 chunks take 38 us so and 78 us in rows of 64 bytes.  Smaller banks with chunks
-  // for every slice take 32 slices of 8 templates.
-  const int T = P.n == 1 ? 1 : a.n_chunks >= 32 && P.n < 65536 ? 8 : 64;
-  const auto fin = T == 1 ? finalize_kernel<1> : T == 8 ? finalize_kernel<8> : finalize_kernel<64>;
+  // for every slice take 32 slices of 8 templates.  The largest banks, and large ones with fewer chunks
+  // than the four slices, take a template per thread (1e7 templates, scan and finalize: 4 groups 0.59 ms
+  // against 0.71 ms, 16 groups 1.30 ms against 1.42 ms; 1e6 x 16 groups 158 us against 152 us); so does
+  // a bank of 2^30 templates or more stay within the 2^32 threads of a grid's row.
+  const bool whole = P.n >= (1 << 22) || (P.n >= 65536 && a.n_chunks < 4);
+  const int T = P.n == 1 ? 1 : whole ? kFinBlock : a.n_chunks >= 32 && P.n < 65536 ? 8 : 64;
+  const auto fin = T == 1 ? finalize_kernel<1> : T == 8 ? finalize_kernel<8> : T == 64 ? finalize_kernel<64>
+                                                                                       : finalize_kernel<kFinBlock>;
   hipLaunchKernelGGL(fin, dim3((unsigned)((P.n + T - 1) / T)), dim3(kFinBlock), 0, st, a.part, a.pflags, P.n,
                      a.n_chunks, P.nacc, P.a_plus, P.a_cross, out->zp, out->zx, out->hhp, out->hhx, out->rho,
                      out->flags, P.xflags, P.nacc == 7 ? out->hhpx : nullptr, P.nacc == 7 ? out->twoF : nullptr,
