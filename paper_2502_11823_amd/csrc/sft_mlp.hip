@@ -769,9 +769,15 @@ hipError_t mlp_infer(const sft_surrogate* s, const double* U, int64_t n, double*
                      int64_t chunk, hipStream_t st)
 {
   const int H = s->d.hidden, L = s->d.layers;
-  if (s->d.inference == SFT_INFER_BF16X3) return n > 0 ? mlp_bf16_launch<true>(s, U, n, Y, dY, st) : hipSuccess;
-  if (s->d.inference == SFT_INFER_BF16) return n > 0 ? mlp_bf16_launch<false>(s, U, n, Y, dY, st) : hipSuccess;
-  if (mlp_fused_ok(H)) return n > 0 ? mlp_fused(s, U, n, Y, dY, st) : hipSuccess;
+  if (mlp_fused_ok(H)) {
+    // four threads per row: launches of 2^28 rows stay within the 2^32 threads that a row of a grid holds
+    const auto fused = s->d.inference == SFT_INFER_BF16X3 ? mlp_bf16_launch<true>
+                       : s->d.inference == SFT_INFER_BF16 ? mlp_bf16_launch<false> : mlp_fused;
+    hipError_t e = hipSuccess;
+    for (int64_t r0 = 0; r0 < n && e == hipSuccess; r0 += 1 << 28)
+      e = fused(s, U + 3 * r0, std::min<int64_t>(n - r0, 1 << 28), Y + 2 * r0, dY + 2 * r0, st);
+    return e;
+  }
   double* b0 = (double*)scratch;
   double* b1 = b0 + (size_t)(2 * chunk) * std::max(H, 3);
   for (int64_t r0 = 0; r0 < n; r0 += chunk) {

@@ -45,3 +45,20 @@ def test_bank_of_more_than_2_30_templates():
     _free(170)
     for k, (a, b) in _ends((1 << 30) + 77, 1, 1).items():
         assert np.array_equal(a, b), k
+
+
+@pytest.mark.parametrize("inference", ["bf16", "bf16x3", "fp64"])
+def test_inference_of_more_than_2_30_rows(inference):
+    _free(80)
+    n = (1 << 30) + 77
+    net = sft.Surrogate(synth.mlp_init(13, 32, 1), hidden=32, layers=1, inference=inference)
+    u = torch.zeros((n, 3), dtype=torch.float64, device="cuda")
+    ends = torch.linspace(-1, 1, 1800, dtype=torch.float64, device="cuda").reshape(600, 3)
+    u[:300], u[-300:] = ends[:300], ends[300:]
+    big, small = net.infer(u), net.infer(ends)
+    torch.cuda.synchronize()
+    for a, b in zip(big, small):
+        assert torch.equal(torch.cat([a[:300], a[-300:]]), b) and torch.equal(a[n // 2], a[300])
+    net.close()
+    del big, u, a
+    torch.cuda.empty_cache()
