@@ -124,7 +124,7 @@ void sft_free_data(sft_data* data);
  * samples [a n, (a+1) n) and starting at t0 + a n dt; a segment holding a non-finite sample is
  * a data gap (missing SFT).  n a power of two: an FFT per segment; other even n (the SFT
  * lengths of Sec. IV, e.g. 106 s at 40 Hz) with a known white PSD: the transform as a convolution
- * (Bluestein) up to n = 8190, the band bins by their defining sum above.
+ * (Bluestein) for n from 82 to 8190, the band bins by their defining sum otherwise.
  */
 typedef struct {
   int32_t n_det;        /* detector series */

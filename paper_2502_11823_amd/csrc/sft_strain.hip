@@ -12,7 +12,7 @@
 // [0, n/2]), with B the mean of the middle order statistic of N unit exponentials.  The median
 // is the sorted block's middle element (ties broken by bin): found by a wavefront-wide sort of
 // the union of 64 neighbouring blocks (half widths w <= 96), or by rank counting per bin.
-// strain_blue_kernel, strain_dft_kernel: other even n with a known white PSD.
+// strain_blue_kernel (n from 82 to 8190), strain_dft_kernel: other even n with a known white PSD.
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -984,19 +984,24 @@ __attribute__((amdgpu_waves_per_eu(LOGS == 6 ? 4 : 1))) void strain_blue_kernel(
   if (tid == 0) keep[row] = gap ? 0 : 1;
 }
 
-// Longer segments whose length is not a power of two: the band bins by their defining sum
+// The other segments whose length is not a power of two (few or many samples): the band bins by their defining sum
 // X[k] = sum_j x_j e^{-2 pi i j k / n} (Eq. d_SFT), one bin per thread, the segment in LDS (read
 // as a broadcast), the twiddle advanced by the rotation e^{-2 pi i k / n} and re-anchored from
-// the exact table W[m] = e^{-2 pi i m / n} every kAnchor samples (rounding drift <= kAnchor eps).
+// the exact table W[m] = e^{-2 pi i m / n} every kAnchor samples (rounding drift <= kAnchor eps).  SHORT segments (n <
+// kBlueMinN), one wavefront each, hold the table in LDS too: kShortAnchor twiddles are one entry times the first powers
+// of the rotation, all from the table, so that nothing drifts and no product waits for the one before (20 k segments
+// of 66 samples, 16 bins: 31 us by the long ones' rotation, 54 us with every twiddle read, 26 us so).
 // The PSD is the given white level (no estimate).
-constexpr int kAnchor = 256;
+constexpr int kAnchor = 256, kShortAnchor = 8;
+
+template <bool SHORT>
 
 __global__ __launch_bounds__(kStrainBlock) void strain_dft_kernel(
     const double* __restrict__ x, int64_t n_total, int32_t n_seg, int32_t n, double dt, double s_white,
     int32_t k_lo, int32_t n_bins, const double2* __restrict__ W, double* __restrict__ bins, double* __restrict__ psd,
     int32_t* __restrict__ keep)
 {
-  extern __shared__ double xl[];   // the segment, n values
+  extern __shared__ __align__(16) double xl[];   // the segment, n values; SHORT: then the table, n pairs (n is even)
   __shared__ int s_bad;
   const int row = blockIdx.x;
   const int det = row / n_seg, seg = row - det * n_seg;
@@ -1009,6 +1014,7 @@ __global__ __launch_bounds__(kStrainBlock) void strain_dft_kernel(
     const double v = xs[j];
     bad = bad || !isfinite(v);
     xl[j] = v;
+    if constexpr (SHORT) reinterpret_cast<double2*>(xl + n)[j] = W[j];
   }
   if (bad) s_bad = 1;
   __syncthreads();
@@ -1021,6 +1027,39 @@ __global__ __launch_bounds__(kStrainBlock) void strain_dft_kernel(
       po[i] = 0.0;
     }
     if (tid == 0) keep[row] = 0;
+    return;
+  }
+  if constexpr (SHORT) {
+    const double2* wl = reinterpret_cast<const double2*>(xl + n);
+    for (int i = tid; i < n_bins; i += blockDim.x) {
+      const int k = k_lo + i;
+      double2 r[kShortAnchor];   // e^{-2 pi i t k / n}
+      int step = 0;
+#pragma unroll
+      for (int t = 0; t < kShortAnchor; ++t) {
+        r[t] = wl[step];
+        step += k;
+        step = step >= n ? step - n : step;
+      }
+      double re = 0.0, im = 0.0;
+      int idx = 0;   // (j k) mod n
+      for (int j = 0; j < n; j += kShortAnchor) {
+        const double2 w0 = wl[idx];
+#pragma unroll
+        for (int t = 0; t < kShortAnchor; ++t) {
+          const double2 wv = t ? cmul(w0, r[t]) : w0;
+          const double xj = j + t < n ? xl[j + t] : 0.0;
+          re = fma(xj, wv.x, re);
+          im = fma(xj, wv.y, im);
+        }
+        idx += step;
+        idx = idx >= n ? idx - n : idx;
+      }
+      bo[2 * i] = dt * re;
+      bo[2 * i + 1] = dt * im;
+      po[i] = s_white;
+    }
+    if (tid == 0) keep[row] = 1;
     return;
   }
   for (int i = tid; i < n_bins; i += blockDim.x) {
@@ -1052,10 +1091,12 @@ __global__ __launch_bounds__(kStrainBlock) void strain_dft_kernel(
 
 static sft_status strain_fail(sft_status st, const char* msg) { return sft_set_error(st, msg); }
 
-// Largest segment length of strain_blue_kernel: L = 8192 points (128 KiB of LDS) hold the n - 1 of the
-// convolution, and the next size does not fit the 160 KiB of a CU.  Above it, up to 16382 samples,
-// the defining sum (strain_dft_kernel).
-constexpr int kBlueMaxN = 8192;
+// Segment lengths of strain_blue_kernel.  L = 8192 points (128 KiB of LDS) hold the n - 1 of the convolution, and the
+// next size does not fit the 160 KiB of a CU.  The smallest transform, L = 512, takes about the same time for every
+// n up to 512, the defining sum (strain_dft_kernel) one that grows with n: 20 k segments, every bin, 36 us against 15
+// us at n = 18, 38 us against 32 us at 66.  Below and above these lengths the defining sum.
+constexpr int kBlueMinN = 82, kBlueMaxN = 8192;
+static bool blue_length(int n) { return (n & (n - 1)) != 0 && n >= kBlueMinN && n <= kBlueMaxN; }
 
 typedef void (*BlueFn)(const double*, int64_t, int32_t, int32_t, double, double, int32_t, int32_t, BlueTables, double*,
                        double*, int32_t*);
@@ -1099,8 +1140,8 @@ static BlueSize blue_size(int n)
 }
 
 // Tables of a segment length n, in long double rounded once to FP64: for n a power of two,
-// tw[j] = e^{-2 pi i j / M} (j < M/2, M = n/2) and rtw[k] = e^{-2 pi i k / n} (k <= M/2); for other
-// n up to kBlueMaxN the tables of strain_blue_kernel; above, W[m] = e^{-2 pi i m / n} (m < n).
+// tw[j] = e^{-2 pi i j / M} (j < M/2, M = n/2) and rtw[k] = e^{-2 pi i k / n} (k <= M/2); for the
+// lengths of strain_blue_kernel its tables; for other n W[m] = e^{-2 pi i m / n} (m < n).
 // Built on a device's first call for n and kept there until the process ends (tens of KB per
 // length, up to 0.4 MB for a length that is no power of two), so that later calls only launch.
 struct TwTables {
@@ -1214,7 +1255,7 @@ static hipError_t twiddle_tables(int n, TwTables& out)
   }
   const long double pi = 3.141592653589793238462643383279502884L;
   TwTables t;
-  if ((n & (n - 1)) != 0 && n <= kBlueMaxN) {
+  if (blue_length(n)) {
     e = upload(blue_tables(n, blue_size(n)), &t.blue);
   } else if ((n & (n - 1)) != 0) {
     std::vector<double2> W(n);
@@ -1267,7 +1308,7 @@ extern "C" sft_status sft_make_sfts(const sft_strain_desc* d, const double* x, d
   TwTables tt;
   hipError_t e = twiddle_tables(n, tt);
   if (e != hipSuccess) return strain_fail(SFT_E_DEVICE, hipGetErrorString(e));
-  if (!pow2 && n <= kBlueMaxN) {
+  if (blue_length(n)) {
     const BlueSize z = blue_size(n);
     BlueTables bt;
     bt.b = tt.blue;
@@ -1286,11 +1327,12 @@ extern "C" sft_status sft_make_sfts(const sft_strain_desc* d, const double* x, d
     return SFT_OK;
   }
   if (!pow2) {
-    const size_t lds = (size_t)n * sizeof(double);
-    if (lds > 65536)
-      e = hipFuncSetAttribute((const void*)strain_dft_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const bool is_short = n < kBlueMinN;
+    const auto fn = is_short ? strain_dft_kernel<true> : strain_dft_kernel<false>;
+    const size_t lds = (size_t)n * (is_short ? sizeof(double) + sizeof(double2) : sizeof(double));
+    if (lds > 65536) e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e == hipSuccess && n_seg > 0) {
-      hipLaunchKernelGGL(strain_dft_kernel, dim3((unsigned)(n_seg * d->n_det)), dim3(kStrainBlock), lds, st, x,
+      hipLaunchKernelGGL(fn, dim3((unsigned)(n_seg * d->n_det)), dim3(is_short ? 64 : kStrainBlock), lds, st, x,
                          d->n_total, (int32_t)n_seg, n, d->dt, d->s_white, d->k_lo, d->n_bins, tt.W, bins, psd, keep);
       e = hipGetLastError();
     }
