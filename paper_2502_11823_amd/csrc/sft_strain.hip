@@ -15,6 +15,7 @@
 // strain_blue_kernel (n from 82 to 8190), strain_dft_kernel: other even n with a known white PSD.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <map>
@@ -1318,10 +1319,17 @@ extern "C" sft_status sft_make_sfts(const sft_strain_desc* d, const double* x, d
     bt.rtw = bt.ws + z.S();
     const size_t lds = (size_t)z.L() * sizeof(double2);
     if (lds > 65536) e = hipFuncSetAttribute((const void*)z.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess && n_seg > 0) {
-      hipLaunchKernelGGL(z.fn, dim3((unsigned)(n_seg * d->n_det)), dim3(z.threads), lds, st, x, d->n_total, (int32_t)n_seg,
-                         M, d->dt, d->s_white, d->k_lo, d->n_bins, bt, bins, psd, keep);
+    // One launch, or with more segments than a grid's row holds (2^32 threads in workgroups of up to 1024) launches of
+    // 2^21 segments of one detector
+    const int64_t rows = n_seg * d->n_det, most = 1 << 21;
+    for (int64_t r0 = 0; r0 < rows && e == hipSuccess;) {
+      const int64_t det = r0 / n_seg, seg = r0 - det * n_seg;
+      const int64_t nr = rows <= most ? rows : std::min(most, n_seg - seg);
+      hipLaunchKernelGGL(z.fn, dim3((unsigned)nr), dim3(z.threads), lds, st, x + det * d->n_total + seg * n, d->n_total,
+                         (int32_t)n_seg, M, d->dt, d->s_white, d->k_lo, d->n_bins, bt, bins + r0 * 2 * d->n_bins,
+                         psd + r0 * d->n_bins, keep + r0);
       e = hipGetLastError();
+      r0 += nr;
     }
     if (e != hipSuccess) return strain_fail(SFT_E_DEVICE, hipGetErrorString(e));
     return SFT_OK;

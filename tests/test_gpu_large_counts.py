@@ -62,3 +62,18 @@ def test_inference_of_more_than_2_30_rows(inference):
     net.close()
     del big, u, a
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n_det", [1, 2])
+def test_segments_of_more_than_one_launch(n_det):
+    """More than 2^21 segments, of a length that takes the convolution."""
+    n, n_seg = 90, ((1 << 21) + 8) // n_det
+    x = torch.zeros((n_det, n * n_seg), dtype=torch.float64, device="cuda")
+    ends = (torch.linspace(-1, 1, n_det * 6 * n, dtype=torch.float64, device="cuda") ** 3).reshape(n_det, 6 * n)
+    x[:, :3 * n], x[:, -3 * n:] = ends[:, :3 * n], ends[:, 3 * n:]
+    big = sft.make_sfts(x, n, 0.025, 5, 3, 0, s_white=0.05)
+    small = sft.make_sfts(ends, n, 0.025, 5, 3, 0, s_white=0.05)
+    torch.cuda.synchronize()
+    for a, b in zip(big, small):
+        assert torch.equal(torch.cat([a[:, :3], a[:, -3:]], 1), b)
+    assert int(big[2].sum()) == n_det * n_seg and not bool(big[0][:, 3:-3].any())
