@@ -158,8 +158,8 @@ __device__ inline void bitonic_from(double& a, int& ia, double& b, int& ib, int 
 // or 8 for E = 2 or 4 keys per lane): ratios down to 2^-32 (2^-16) keep all 20 mantissa bits of the word, smaller
 // values share one key value.  A compare-exchange then is one lane exchange and one instruction instead of three
 // exchanges and a 64-bit compare with its selects.  The median found so is exact unless the entry beside it
-// in the sorted list has the same upper word (one chunk in thousands on noise): then the caller takes the
-// exact path for the whole chunk (the sort of pairs, or rank counting for w > 32).  12288 segments of 4096
+// in the sorted list has the same upper word (one chunk in thousands on noise): then, unless those are zeros, the
+// caller takes the exact path for the whole chunk (the sort of pairs, or rank counting for w > 32).  12288 segments of 4096
 // samples, w = 25: 274 us with the pairs alone, 186 us so; 1000 of 1024 samples, w = 50: 510 us by rank
 // counting, 15 us so.
 template <int E>
@@ -250,8 +250,18 @@ __device__ inline bool key_medians(const double* U, int u0, int L, int s0r, int 
   }
   top = wave_max(top);
   bot = ~wave_max(bot);
-  // one key value for all, or an infinity or NaN
-  if (top == bot || top >= 0x7ff00000u) return false;
+  if (top >= 0x7ff00000u) return false;   // an infinity or NaN
+  if (top == bot) {
+    // one key value for all; one value for all (a detector that recorded zeros): that is every median
+    bool same = true;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int p = 64 * e + lane;
+      same = same && (p >= L || U[u0 + p] == U[u0]);
+    }
+    med = U[u0];
+    return !__ballot(!same);
+  }
   const uint32_t base = top > KS::R ? top - KS::R : 0;
 #pragma unroll
   for (int e = 0; e < E; ++e) {
@@ -309,7 +319,19 @@ __device__ inline bool key_medians(const double* U, int u0, int L, int s0r, int 
   const bool tie = (kp >> KS::B) == (kq >> KS::B) || (kn >> KS::B) == (kq >> KS::B);
   med = U[u0 + (int)(kq & (KS::N - 1))];
   wave_sync();
-  return !__ballot(want && tie);
+  if (!__ballot(want && tie)) return true;
+  // ties among zeros (a constant segment's bins beside its mean): every entry of the lowest key value is 0 (7812
+  // such segments of 256 samples, w = 25: pairs alone 37 us, keys and then pairs 50 us, so 29 us)
+  bool zeros = !(want && tie) || (kq >> KS::B) == 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int p = 64 * e + lane;
+    if (p < L) {
+      const double v = U[u0 + p];
+      zeros = zeros && (v == 0.0 || (uint32_t)((unsigned long long)__double_as_longlong(v) >> 32) > base);
+    }
+  }
+  return !__ballot(!zeros);
 }
 
 // The exact path: the medians by a sort of (value, bin) pairs, L <= kSortN.
