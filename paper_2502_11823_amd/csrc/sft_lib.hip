@@ -1214,23 +1214,24 @@ __device__ inline double psd_at(const PS* __restrict__ psd, int r, double kappa,
 // chirps for a rejected template).  The judge's weight of SFT row r is A_PN^2 T / S_r(f_PN) (the
 // row's share of <h,h>); rows whose PSD is masked or outside the stored band at f_PN carry no weight.
 //
-// Bound: FP64 arithmetic of the two chirps.  A workgroup takes kPostT templates and spreads the groups
-// over kPostS slices (slice s takes the groups s, s + kPostS, ...; the judge's sums are combined over
-// the slices by a fixed tree in LDS).  One lane per template left half of the chip without work and
-// the rest with one wavefront per SIMD: 880 us for 32768 templates x 256 groups, 325 us so.
-constexpr int kPostT = 16, kPostS = 16;
+// Bound: FP64 arithmetic of the two chirps.  A workgroup takes 256 / NS templates and spreads the groups
+// over NS slices (slice s takes the groups s, s + NS, ...; the judge's sums are combined over
+// the slices by a fixed tree in LDS).  One lane per template leaves half of the chip without work and
+// the rest with one wavefront per SIMD where a batch has few templates: 880 us for 32768 templates x 256
+// groups, 325 us with slices.
+constexpr int kPostBlock = 256;
 
-template <typename PS>
-__global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
+template <typename PS, int NS>
+__global__ __launch_bounds__(kPostBlock) void sur_post_kernel(
     SurArgs sa, const double* __restrict__ mc, const double* __restrict__ q, const double* __restrict__ t_c,
     const double* __restrict__ phi_c, const int32_t* __restrict__ a_first, const int32_t* __restrict__ a_last,
     const double* __restrict__ g_tmid, const int32_t* __restrict__ g_rows, int64_t nb, int32_t n_groups, double T,
     const double* __restrict__ Y, const double* __restrict__ dY, double* __restrict__ tab, uint32_t* __restrict__ xflags,
     double* __restrict__ mismatch, const PS* __restrict__ psd, int32_t k_lo, int32_t n_bins)
 {
-  __shared__ double red[3][kPostT * kPostS];
-  const int slice = threadIdx.x / kPostT;
-  const int64_t m_ = (int64_t)blockIdx.x * kPostT + threadIdx.x % kPostT;
+  constexpr int NT = kPostBlock / NS;   // templates
+  const int slice = threadIdx.x / NT;
+  const int64_t m_ = (int64_t)blockIdx.x * NT + threadIdx.x % NT;
   const bool valid = m_ < nb;
   const int64_t m = valid ? m_ : nb - 1;   // a lane past the end repeats the last template and stores nothing
   const int lo = a_first ? (int)a_first[m] : 0;
@@ -1260,7 +1261,7 @@ __global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
     w[4 * ps] = c.dres;
   };
   double sr = 0.0, si = 0.0, sw = 0.0;
-  for (int g = slice; g < n_groups; g += kPostS) {
+  for (int g = slice; g < n_groups; g += NS) {
     const double tau = tc - g_tmid[g];
     if (!used(g) || !(tau > 0.0)) continue;
     const int64_t r = (int64_t)g * nb + m;
@@ -1310,19 +1311,22 @@ __global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
     si += wt * sd * snc;
     sw += wt;
   }
-  red[0][threadIdx.x] = sr;
-  red[1][threadIdx.x] = si;
-  red[2][threadIdx.x] = sw;
-  for (int h = kPostS / 2; h > 0; h >>= 1) {
+  if constexpr (NS > 1) {
+    __shared__ double red[3][kPostBlock];
+    red[0][threadIdx.x] = sr;
+    red[1][threadIdx.x] = si;
+    red[2][threadIdx.x] = sw;
+    for (int h = NS / 2; h > 0; h >>= 1) {
+      __syncthreads();
+      if (slice < h)
+        for (int i = 0; i < 3; ++i) red[i][threadIdx.x] += red[i][threadIdx.x + h * NT];
+    }
     __syncthreads();
-    if (slice < h)
-      for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + h * kPostT];
+    const int col = threadIdx.x % NT;
+    sr = red[0][col];
+    si = red[1][col];
+    sw = red[2][col];
   }
-  __syncthreads();
-  const int col = threadIdx.x % kPostT;
-  sr = red[0][col];
-  si = red[1][col];
-  sw = red[2][col];
   const double mm = sw > 0.0 ? 1.0 - sqrt(sr * sr + si * si) / sw : 0.0;
   const bool fallback = !(mm <= sa.judge_tol);
   if (!valid) return;
@@ -1331,7 +1335,7 @@ __global__ __launch_bounds__(kPostT * kPostS) void sur_post_kernel(
     xflags[m] = fallback ? kFlagSurrogateFallback : 0u;
   }
   if (!fallback) return;
-  for (int g = slice; g < n_groups; g += kPostS) {
+  for (int g = slice; g < n_groups; g += NS) {
     const double tau = tc - g_tmid[g];
     if (!used(g) || !(tau > 0.0)) continue;
     store(g, pn35_chirp(tau, pm.nu, pm.inv5Mnu, pm.Mt, pm.nu25, phic, T, pc));
@@ -1359,6 +1363,15 @@ static int64_t sur_batch(int64_t n, int32_t n_groups)
   int64_t b = ((int64_t)1 << 23) / std::max(1, n_groups);
   b = std::max<int64_t>(256, b / 256 * 256);
   return std::min(b, n);
+}
+
+// Slices of sur_post_kernel for a batch of nb templates: as many as bring the chip its 131072 resident lanes, and no
+// more, as every slice repeats its template's setup and few groups leave slices idle.  Whole scans in us by slices (1,
+// 4, 16): 3 k templates x 60 groups 161, 68, 46; 30 k x 60 238, 162, 168; 140 k x 60 at a time 1994, 1715, 1769;
+// 300 k x 8 218, 231, 336; 1 M x 1 139, 241, 677.
+static int post_slices(int64_t nb, int32_t n_groups)
+{
+  return n_groups < 4 || nb > (1 << 18) ? 1 : nb > (1 << 14) ? 4 : 16;
 }
 
 // Scan with the surrogate waveform, batch by batch: network inputs, FP64 network
@@ -1420,14 +1433,18 @@ static sft_status surrogate_scan(const sft_data* d, const sft_bank* bank, int64_
                        d->g_tmid, nb, d->n_groups, U);
     if ((e = hipGetLastError()) != hipSuccess) break;
     if ((e = mlp_infer(sur, U, rows, Y, dY, ws + off_nn, chunk, st)) != hipSuccess) break;
+    const int S = post_slices(nb, d->n_groups);
+    const dim3 pg((unsigned)((nb * S + kPostBlock - 1) / kPostBlock)), pb(kPostBlock);
     if (d->storage == SFT_STORE_F64)
-      hipLaunchKernelGGL(sur_post_kernel<double>, dim3((unsigned)((nb + kPostT - 1) / kPostT)), dim3(kPostT * kPostS), 0, st, sa, b.mc, b.q,
-                         b.t_c, b.phi_c, b.a_first, b.a_last, d->g_tmid, d->g_rows, nb, d->n_groups, d->T, Y, dY, tab,
-                         xf, ob.mismatch, (const double*)d->psd, d->k_lo, d->n_bins);
+      hipLaunchKernelGGL((S == 16 ? sur_post_kernel<double, 16> : S == 4 ? sur_post_kernel<double, 4>
+                                                                         : sur_post_kernel<double, 1>),
+                         pg, pb, 0, st, sa, b.mc, b.q, b.t_c, b.phi_c, b.a_first, b.a_last, d->g_tmid, d->g_rows, nb,
+                         d->n_groups, d->T, Y, dY, tab, xf, ob.mismatch, (const double*)d->psd, d->k_lo, d->n_bins);
     else
-      hipLaunchKernelGGL(sur_post_kernel<float>, dim3((unsigned)((nb + kPostT - 1) / kPostT)), dim3(kPostT * kPostS), 0, st, sa, b.mc, b.q,
-                         b.t_c, b.phi_c, b.a_first, b.a_last, d->g_tmid, d->g_rows, nb, d->n_groups, d->T, Y, dY, tab,
-                         xf, ob.mismatch, (const float*)d->psd, d->k_lo, d->n_bins);
+      hipLaunchKernelGGL((S == 16 ? sur_post_kernel<float, 16> : S == 4 ? sur_post_kernel<float, 4>
+                                                                        : sur_post_kernel<float, 1>),
+                         pg, pb, 0, st, sa, b.mc, b.q, b.t_c, b.phi_c, b.a_first, b.a_last, d->g_tmid, d->g_rows, nb,
+                         d->n_groups, d->T, Y, dY, tab, xf, ob.mismatch, (const float*)d->psd, d->k_lo, d->n_bins);
     if ((e = hipGetLastError()) != hipSuccess) break;
     Prepared P;
     if ((s = prepare_scan(d, &b, nb, o, d->tune, P, false, WF_TABLE, tab, xf)) != SFT_OK) break;
