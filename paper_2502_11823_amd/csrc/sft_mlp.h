@@ -19,6 +19,7 @@ struct sft_surrogate {
   void* frag;         // BF16 inference: the hidden-to-hidden weights as packed MFMA fragments (or null)
   int32_t step;       // Adam step count
   int device;
+  int cu_count;       // compute units of the device
 };
 
 // record msg as the thread's last error (sft_last_error) and return st

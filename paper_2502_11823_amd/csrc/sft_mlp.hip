@@ -597,9 +597,9 @@ __device__ inline void split_bf16(float x0, float x1, bf16x8& hi, bf16x8& lo, in
 // Bound: instruction issue.  A wavefront's 16 rows cost 192 MFMAs (4 issue cycles and 16 on the matrix cores
 // each) and 610 vector instructions a layer (SiLU with its derivative, 64 of the latter at a quarter rate, and
 // the split of the activations), so that the matrix cores wait unless other wavefronts of the SIMD fill in.
-// NW wavefronts per workgroup share the fragments in LDS: with split operands 12 of them (3 per SIMD within
-// 168 VGPRs, one workgroup of 128 KiB per CU), plain ones 8 (two workgroups per CU).  8.4 M rows of
-// 3 -> 128 x 4 -> 2, split: one wavefront per SIMD with 32 rows each 5.6 ms, 8 with 16 rows 4.8 ms, 12 4.5 ms.
+// NW wavefronts per workgroup share the fragments in LDS: at 128 units up to 12 of them, 3 per SIMD within 168
+// VGPRs (142 with plain operands), one workgroup of 128 KiB (64 KiB) per CU.  8.4 M rows of 3 -> 128 x 4 -> 2, split:
+// one wavefront per SIMD with 32 rows each 5.6 ms, 8 with 16 rows 4.8 ms, 12 4.5 ms; plain: 3.1, 3.2 and 2.95 ms.
 // The fragments are double buffered: layer l + 1's are loaded into LDS while layer l runs (the
 // layer's biases are read into registers before that prefetch is issued, so that waiting for
 // them does not wait for it).
@@ -724,7 +724,9 @@ __global__ __launch_bounds__(64 * NW) void mlp_bf16_kernel(const double* __restr
 // Wavefronts per workgroup.  Widths below 128 take 8 (several workgroups share a CU: 64 units, 300 k rows, split
 // 50 us with 8 and 59 us with 12).  At 128 units a CU holds one workgroup, whose time is about 1.8 us times
 // 2.6 + its wavefronts (split, 3 hidden-to-hidden layers: 11.8, 18.6 and 26.4 us for 4, 8 and 12), so the size
-// with the least rounds x time over the 256 CUs is taken: 12 for large n, 8 for 50 k rows (37 us, 12: 53 us).
+// with the least rounds x time over the device's CUs is taken: 12 for large n, 8 for 50 k rows (37 us, 12: 53 us).
+// Plain operands go by the same rule: two of their workgroups of 4 share a CU, which the rule does not know, and 100 k
+// to 500 k rows would be 2 to 16% faster so (300 k rows 113 us, 12: 119 us); 1 M rows 381, 398 and 376 us for 4, 8, 12.
 template <int NT, bool SPLIT>
 static void mlp_bf16_go(const sft_surrogate* s, const double* U, int64_t n, double* Y, double* dY, hipStream_t st)
 {
@@ -732,7 +734,8 @@ static void mlp_bf16_go(const sft_surrogate* s, const double* U, int64_t n, doub
   const int L = s->d.layers;
   int nw = 8;
   if constexpr (NT == 8) {
-    auto cost = [&](int w) { return (double)((n + 4096 * w - 1) / (4096 * w)) * (2.6 + w); };
+    const int64_t rows = 16 * (int64_t)s->cu_count;   // of a round of single wavefronts
+    auto cost = [&](int w) { return (double)((n + rows * w - 1) / (rows * w)) * (2.6 + w); };
     for (int w : {12, 4})
       if (cost(w) < cost(nw)) nw = w;
   }
@@ -1475,6 +1478,8 @@ extern "C" sft_status sft_surrogate_create(const sft_surrogate_desc* d, const fl
   s->d = *d;
   s->P = mlp_param_count(d->hidden, d->layers);
   hipError_t e = hipGetDevice(&s->device);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&s->cu_count, hipDeviceAttributeMultiprocessorCount, s->device);
+  if (s->cu_count < 1) s->cu_count = 256;
   if (e == hipSuccess) e = hipMalloc(&s->par, s->P * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&s->grad, s->P * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&s->mom1, s->P * sizeof(float));
