@@ -158,7 +158,8 @@ struct sft_data {
                           // set, every group holds one row
   double* row_tmid;       // [n_sft] midpoint t_start + T/2 of each row (bank ordering)
   mutable std::mutex ip_mu;
-  mutable std::vector<IpSlot> ip_free;   // blocks of sft_inner_product not in use
+  mutable IpSlot ip_free[kIpSlots];   // the first ip_count: blocks of sft_inner_product not in use
+  mutable size_t ip_count;
 };
 
 static void ip_destroy(const IpSlot& s)
@@ -176,9 +177,8 @@ static sft_status ip_acquire(const sft_data* d, IpSlot& s)
   s.keep = e == hipSuccess && dev == d->device;
   if (s.keep) {
     std::lock_guard<std::mutex> lk(d->ip_mu);
-    if (!d->ip_free.empty()) {
-      s = d->ip_free.back();
-      d->ip_free.pop_back();
+    if (d->ip_count > 0) {
+      s = d->ip_free[--d->ip_count];
       return SFT_OK;
     }
   }
@@ -193,8 +193,8 @@ static void ip_release(const sft_data* d, const IpSlot& s)
 {
   if (s.keep) {
     std::lock_guard<std::mutex> lk(d->ip_mu);
-    if (d->ip_free.size() < kIpSlots) {
-      d->ip_free.push_back(s);
+    if (d->ip_count < kIpSlots) {
+      d->ip_free[d->ip_count++] = s;
       return;
     }
   }
@@ -275,7 +275,7 @@ static void build_groups(const double* t_start, int32_t n_sft, double T, std::ve
 static sft_status load_device(const sft_data_desc* d, const double* t_start, const double* dx, const double* dp,
                               const double* fplus, const double* fcross, hipStream_t st, sft_data** out)
 {
-  sft_data* h = new sft_data();   // value-initialised: null pointers
+  sft_data* h = new sft_data();   // value-initialised: null pointers, no blocks
   HIP_OR_FAIL(hipGetDevice(&h->device));
   if (hipDeviceGetAttribute(&h->cu_count, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess ||
       h->cu_count < 1)
@@ -492,7 +492,7 @@ extern "C" void sft_free_data(sft_data* h)
   if (h->fx) (void)hipFree(h->fx);
   if (h->g_eph) (void)hipFree(h->g_eph);
   if (h->row_tmid) (void)hipFree(h->row_tmid);
-  for (const IpSlot& s : h->ip_free) ip_destroy(s);
+  while (h->ip_count > 0) ip_destroy(h->ip_free[--h->ip_count]);
   delete h;
 }
 
