@@ -358,7 +358,8 @@ enum { SFT_ORDER_GIVEN = 0, SFT_ORDER_TRACK = 1 };
  * the groups per resident workgroup).  persistent: 1 launches one workgroup per
  * resident slot, each pulling work items from a device counter until the queue is empty; 0
  * launches one workgroup per item.  An all-zero tuning selects the automatic chunks with one
- * workgroup per item, and with FP64 Fresnel weights the persistent grid.
+ * workgroup per item, and the persistent grid with FP64 Fresnel weights and with wide Fresnel
+ * windows (K >= 24) of 3.5PN templates on single SFT rows.
  * order: SFT_ORDER_GIVEN scans the bank in the caller's order, which is fast when
  * neighbouring templates have nearly equal frequency tracks (a bank sorted by chirp mass at
  * one coalescence time, say).  SFT_ORDER_TRACK first sorts the bank on the device by (first

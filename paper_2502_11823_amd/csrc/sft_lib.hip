@@ -846,12 +846,14 @@ static void layout_ws(Prepared& P)
 }
 
 // The grid of the automatic launch shape: plain, as the items come in the same order without the counter (1000
-// templates on three detectors 163 us against 172 us, 200 k space-like 453 and 453 us), but persistent with the FP64
-// Fresnel weights, whose long items a plain grid hands out worse (100 k Newtonian templates x 60 groups 3.10 ms
-// against 2.97 ms, 10 k 3.5PN ones 0.58 ms against 0.50 ms).
-static int auto_persistent(const sft_opts* o)
+// templates on three detectors 163 us against 172 us, 200 k space-like 453 and 453 us), but persistent where a plain
+// grid hands out the long items worse: with the FP64 Fresnel weights (100 k Newtonian templates x 60 groups 3.10 ms
+// against 2.97 ms, 10 k 3.5PN ones 0.58 ms against 0.50 ms) and with wide Fresnel windows of 3.5PN templates on single
+// rows, which are gathered bin by bin (20 k x 1024 groups, K = 50: 3.33 ms against 3.22 ms).
+static int auto_persistent(const sft_data* d, const sft_opts* o)
 {
-  return o->precision == SFT_PREC_FP64 && o->kernel != SFT_KERNEL_DIRICHLET;
+  if (o->kernel == SFT_KERNEL_DIRICHLET) return 0;
+  return o->precision == SFT_PREC_FP64 || (o->waveform == SFT_WF_PN35 && d->nd == 1 && o->K >= 24);
 }
 
 static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t n, const sft_opts* o,
@@ -927,7 +929,7 @@ static sft_status prepare_scan(const sft_data* d, const sft_bank* bank, int64_t 
   if ((int64_t)a.n_tiles * a.n_chunks > INT32_MAX) return fail(SFT_E_RANGE, "scan: too many work items");
   a.n_items = a.n_tiles * a.n_chunks;
   const bool automatic = t.block == 0 && t.chunk_groups == 0 && t.persistent == 0;
-  a.persistent = automatic ? auto_persistent(o) : t.persistent;
+  a.persistent = automatic ? auto_persistent(d, o) : t.persistent;
   P.block = dim3(B);
   if (a.persistent) P.grid = dim3((unsigned)std::min<int64_t>(a.n_items, resident));
   else P.grid = dim3((unsigned)a.n_tiles, (unsigned)a.n_chunks);
@@ -1547,7 +1549,7 @@ extern "C" sft_status sft_template_bank_scan_noalloc(const sft_data* d, const sf
     if (nc_max < 1)
       return fail(SFT_E_RANGE, "scan (no-alloc): %lld templates need %zu bytes of partial sums, more than the %u-byte scratch",
                   (long long)n, per_chunk, (unsigned)SFT_NOALLOC_SCRATCH_BYTES);
-    if (t.block == 0 && t.chunk_groups == 0 && t.persistent == 0) t.persistent = auto_persistent(o);   // the automatic grid
+    if (t.block == 0 && t.chunk_groups == 0 && t.persistent == 0) t.persistent = auto_persistent(d, o);   // the automatic grid
     t.chunk_groups = (int32_t)((d->n_groups + nc_max - 1) / nc_max);
     if ((s = prepare_scan(d, bank, n, o, t, P, fs)) != SFT_OK) return s;
     if (P.ws_bytes > SFT_NOALLOC_SCRATCH_BYTES)
