@@ -127,9 +127,9 @@ __device__ inline double log64(double x)
   p = fma(p, z, 1.0 / 7);
   p = fma(p, z, 1.0 / 5);
   p = fma(p, z, 1.0 / 3);
-  const double ln2hi = 0.693147180369123816490, ln2lo = 1.90821492927058770002e-10;   // hi has 21 zero bits
+  const double ln2hi = 0.69314718055994530942, ln2lo = 2.3190468138462996e-17;   // the nearest double, ln 2 - ln2hi
   const double lm = fma(2.0 * f * z, p, 2.0 * f);
-  return fma((double)e, ln2hi, fma((double)e, ln2lo, lm));
+  return fma((double)e, ln2hi, fma((double)e, ln2lo, lm));   // e ln2hi is exact inside the fma
 }
 
 // sin(pi x) / (pi x) for |x| <= 1/2, as a function of z = x^2 (Maclaurin series to x^20)
