@@ -89,9 +89,11 @@ template <> struct BinIO<bf16x2> {
 };
 
 // ---------------------------------------------------------------- FP64 functions
-// The FP64 paths are bound by FP64 instructions, most of them special functions; the ones below are for
-// the ranges that occur and leave out what the library has to have (large arguments, subnormals, exact rounding:
-// no branches), within two ulp.  30 k 3.5PN templates x 256 SFTs in FP64: 243 us with the library's, 195 us so.
+// Special functions are a large part of the FP64 Dirichlet scans' instructions; the ones below are for the ranges
+// that each of them names and leave out what the library has to have (large arguments, subnormals, exact rounding:
+// no branches), within about two ulp.  30 k 3.5PN templates x 256 SFTs in FP64: 243 us with the library's, 199 us so.
+// That scan issues for some 80 us (245 FP64 of 420 vector instructions a group); the rest of its time is the latency
+// of its nine bins, each loaded and waited for in turn.
 
 // 1 / x and 1 / sqrt(x), x normal: the hardware estimate and two Newton steps
 __device__ inline double rcp64(double x)

@@ -154,7 +154,9 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
 // 4096 groups of 3 rows in chunks of 4, against 20 us at one group a lane).  The groups' terms go
 // to LDS, and one lane per chunk and sum adds them in group order, so that the sums are those of the
 // general kernel.  Lanes hold different rows, so the bins are gathered, and the series bounds are each
-// lane's own, which is what the wavefront of a single template uses.
+// lane's own, which is what the wavefront of a single template uses.  In the kernels with compile-time Fresnel windows
+// (and the 3.5PN Dirichlet one of four rows) the compiler makes a function of the group's terms, which are asked for
+// in two places: its arguments go through 256 bytes of scratch a lane.
 template <typename R>
 struct AccTerm {   // the one term of a lane's group
   R s = 0;

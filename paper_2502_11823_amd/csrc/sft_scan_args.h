@@ -66,7 +66,7 @@ ScanFn scan_pick_fstat(int prec, int kern, int K, int nd);
 ScanFn scan_pick_doppler(int prec, int fs, int kern, int K);
 // the Taylor expansion at the SFT start (run-time window)
 ScanFn scan_pick_start(int storage, int prec, int wf, int kern, int nd, int fs);
-// a bank of one template: chunk c of the timestamp groups on lane c of the grid (closed-form waveforms at
+// a bank of one template: one timestamp group per lane, 64 / chunk chunks per wavefront (closed-form waveforms at
 // the midpoint; FP32-Kahan sums on F32 storage, FP64 sums on F64 storage)
 ScanFn scan_pick_one_f32(int wf, int kern, int K, int nd);
 ScanFn scan_pick_one_f64(int wf, int kern, int K, int nd);

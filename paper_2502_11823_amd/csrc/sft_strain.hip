@@ -691,7 +691,7 @@ __global__ __launch_bounds__(kStrainBlock) void strain_sft_kernel(
 // L = R0 S with R0 in {8, 9, 10, 12} (16 for the largest) and S in {64, 128, 256, 512}: a first
 // pass of radix R0 and passes of radix 8 (2 or 4 for the leftover bits) over the R0 sub-transforms
 // of S points.  A power of two alone would take 8192 points where 4608 do (106 s at 40 Hz: M =
-// 2120), twice the LDS traffic and one workgroup per CU instead of two.
+// 2120), nearly twice the LDS traffic.
 //
 // Bound: LDS traffic.  Of the eight passes, the first reads the strain itself, the last of the
 // forward transform, the multiplication with the spectrum of b and the first of the inverse run
@@ -829,7 +829,8 @@ __device__ inline void dft_any(double2* v)
   }
 }
 
-// The powers w, w^2 .. w^(R-1) of a root, each from the two halves of its exponent (at most three products deep)
+// The powers w, w^2 .. w^(R-1) of a root, each from the two halves of its exponent (three products deep for R <= 9,
+// four above)
 template <int R>
 __device__ inline void powers(double2 w, double2* p)
 {
@@ -922,7 +923,8 @@ struct BlueTables {
 
 // One workgroup per segment; the PSD is the given white level (no estimate).
 template <int R0, int LOGS>
-// (S = 64 held to 128 registers, four wavefronts per SIMD: 20 k segments of 602 samples 109 -> 94 us)
+// (S = 64 held to 128 registers, four wavefronts per SIMD, at 16 to 20 bytes of scratch a lane: 20 k segments of 602
+// samples 109 -> 94 us.  The 16 wavefronts of the largest size, L = 8192, leave 128 registers each and spill 148 bytes.)
 __global__ __launch_bounds__((BlueShape<R0, LOGS>::threads))
 __attribute__((amdgpu_waves_per_eu(LOGS == 6 ? 4 : 1))) void strain_blue_kernel(
     const double* __restrict__ x, int64_t n_total, int32_t n_seg, int32_t M, double dt, double s_white, int32_t k_lo,
