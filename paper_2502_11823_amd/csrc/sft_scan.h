@@ -287,7 +287,7 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
   using R = typename PrecTraits<PREC>::R;
   using Acc = typename std::conditional<ONE != 0, AccTerm<R>, typename PrecTraits<PREC>::Acc>::type;
   using PS = typename std::conditional<PREC == SFT_PREC_FP64, double, float>::type;
-  // The FP64 Dirichlet kernels take their own sine and cosine and the bins in pairs.  The FP64 Fresnel kernels keep the
+  // The FP64 Dirichlet kernels take their own functions and the bins in pairs.  The FP64 Fresnel kernels keep the
   // library's and the bins one by one (for the drifts below beta_switch): their time goes into the Fresnel weights, and
   // the registers of the other form cost them a wavefront per SIMD (100 k Newtonian templates x 60 groups 2.98 ms so,
   // 3.50 ms with it) and the 3.5PN ones up to 92 bytes of scratch.
@@ -384,7 +384,7 @@ __device__ __forceinline__ uint32_t scan_item(const ScanArgs& a, const int K, co
     }
     Chirp ch;
     if constexpr (WF == WF_PN35) {
-      ch = pn35_chirp(tau, nu, inv5Mnu, Mt, nu25, phic, T, pcf);
+      ch = pn35_chirp<PREC == SFT_PREC_FP64 && KERN == KERN_FRESNEL>(tau, nu, inv5Mnu, Mt, nu25, phic, T, pcf);
     } else if constexpr (WF == WF_TABLE) {
       const int64_t ps = (int64_t)a.n_groups * a.n_tmpl;
       const double* w = a.wtab + (int64_t)g * a.n_tmpl + m;
