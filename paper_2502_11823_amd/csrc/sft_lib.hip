@@ -1284,7 +1284,8 @@ __global__ __launch_bounds__(kPostBlock) void sur_post_kernel(
     cs.phase = cn.phase + dphi;
     cs.amp = cn.amp * exp(sa.c_amp * y2);
     const double kr = cs.kappa / cn.kappa, kr2 = kr * kr;
-    cs.beta = cn.beta * kr2 * kr2 * inv_root3(kr);   // beta ~ kappa^(11/3)
+    // beta ~ kappa^(11/3); inv_root3 starts from an FP32 estimate, whose range a diverged network may leave
+    cs.beta = cn.beta * (kr > 1e-30 && kr < 1e30 ? kr2 * kr2 * inv_root3(kr) : pow(kr, 11.0 / 3.0));
     cs.dres = (11.0 / 24.0) * cs.beta * cs.beta / cs.kappa;
     if (valid) store(g, cs);
     // judge term: A_PN^2 T / S_r(f_PN) exp(i dphi) sinc(dkappa), summed over the group's rows

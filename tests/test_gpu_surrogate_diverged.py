@@ -31,3 +31,23 @@ def test_diverged_network_falls_back(scale, inference):
     o = orc_scan(w, bank, waveform="pn35", **kw)
     o["flags"] = o["flags"] | oracle.F_SURROGATE_FALLBACK
     compare(g, o, label="diverged %g %s" % (scale, inference), tol_z=1e-9, tol_rho=1e-9, tol_hh=1e-9)
+
+
+@pytest.mark.parametrize("c_phi", [2.0, 1e20])
+def test_diverged_network_accepted(c_phi):
+    """A tolerance above 1 accepts every chirp: those far above every band are flagged for it and for their drift."""
+    w = synth.tiny(seed=1, n_templates=1, n_sft=8, noise_series=False)
+    bank = synth.uniform_bank(37, 1.19, 1.21, 8 * 64.0 + 600.0, 9, q_lo=1.0, q_hi=2.0, n_sft=w.n_sft)
+    par = synth.mlp_init(13, 32, 2)
+    par[-66:] *= 1e30
+    cfg = dict(mc_lo=1.19, mc_hi=1.21, q_lo=1.0, q_hi=2.0, lt_lo=float(np.log(600.0)), lt_hi=float(np.log(1200.0)),
+               c_phi=c_phi, c_amp=1e-35, judge_tol=2.0, head=1)
+    oracle.set_surrogate(par, cfg, 32, 2)
+    s = sft.Surrogate(par, hidden=32, layers=2, head=1, mc=(1.19, 1.21), q=(1.0, 2.0), ln_tau=(cfg["lt_lo"], cfg["lt_hi"]),
+                      c_phi=c_phi, c_amp=1e-35, judge_tol=2.0)
+    kw = dict(K=4, kernel="dirichlet", waveform="surrogate", delta_max=1.0, surrogate=s)
+    g = gpu_scan(sft.SFTData.from_workload(w, storage="f64"), bank, precision="fp64", **kw)
+    s.close()
+    o = orc_scan(w, bank, **kw)
+    assert np.array_equal(g["flags"], o["flags"]) and np.array_equal(g["n_used"], o["n_used"])
+    assert np.any(o["flags"] & oracle.F_OUT_OF_BAND) and np.any(o["flags"] & oracle.F_TAYLOR_INVALID)
