@@ -951,7 +951,8 @@ __device__ inline uint32_t shuffled_row(uint32_t i, uint32_t n, int h, uint32_t 
 //   train_rows_kernel  forward, loss and input gradients of 16 rows per workgroup;
 //   train_grad_kernel  every weight and bias gradient, in slices of the batch;
 //   train_step_kernel  the slices summed in order, Adam, and the loss.
-// Workspace of a batch padded to Bp rows (a multiple of 16; the padding has no gradient).
+// Workspace of a batch padded to Bp rows (a multiple of 16; the padding is stored as zeros, whatever a row of zero
+// inputs gives, infinities among it).
 struct StepBuf {
   float* U;      // [Bp][3] the batch's inputs
   float* Hs;     // [L][Bp][H] outputs of the hidden layers
@@ -1041,7 +1042,7 @@ __global__ __launch_bounds__(64 * NT) void train_rows_kernel(const float* __rest
   };
   auto put = [&](float* lds, float* glb, int l, flt4m v) {
     *reinterpret_cast<flt4m*>(lds + li * HP + ub) = v;
-    *reinterpret_cast<flt4m*>(glb + ((int64_t)l * Bp + row) * H + ub) = v;
+    *reinterpret_cast<flt4m*>(glb + ((int64_t)l * Bp + row) * H + ub) = valid ? v : flt4m{0.0f, 0.0f, 0.0f, 0.0f};
   };
   if (layers > 1) load_fwd(a, 1);
   flt4m hv, dv;
